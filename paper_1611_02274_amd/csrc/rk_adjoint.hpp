@@ -408,10 +408,10 @@ __attribute__((amdgpu_waves_per_eu(WavesPerEu<Prob>::value))) void taped_kernel(
                                                            int32_t* __restrict__ status,
                                                            int32_t* __restrict__ stats,
                                                            TapeView T,
-                                                           const int32_t* __restrict__ order) {
+                                                           const int32_t* __restrict__ order,
+                                                           int lanes) {
   __shared__ double lds[kernel_lds_doubles<Prob, Method>() * kLdsStride];
-  const int64_t q = (int64_t)blockIdx.x * kLdsStride + threadIdx.x;
-  if (q >= n) return;
+  const int64_t q = spread_position(n, lanes);
   const int64_t i = order ? (int64_t)order[q] : q;   // lane q integrates system order[q]
   taped_system<Prob, Method>(prm, n, i, y0, y1, g, c, status, stats, T, lds + threadIdx.x);
 }
@@ -433,14 +433,15 @@ __global__ __launch_bounds__(kLdsStride) void adjoint_kernel(typename Prob::Para
                                                              double* __restrict__ dth,
                                                              int32_t* __restrict__ status,
                                                              double* cols,
-                                                             const int32_t* __restrict__ order) {
+                                                             const int32_t* __restrict__ order,
+                                                             int lanes) {
   __shared__ double lds[adjoint_lds_doubles<Prob, Method>() * kLdsStride];
-  const int64_t q = (int64_t)blockIdx.x * kLdsStride + threadIdx.x;
-  if (q >= n) return;
+  const int64_t q = spread_position(n, lanes);
   const int64_t i = order ? (int64_t)order[q] : q;   // lane q sweeps system order[q]
+  // (the columns of position q; copies of a system share them)
   double* const col = cols +
-                      (int64_t)blockIdx.x * adjoint_rows<Prob, Method>(max_stages, T.K) * kLdsStride +
-                      threadIdx.x;
+                      q / kLdsStride * adjoint_rows<Prob, Method>(max_stages, T.K) * kLdsStride +
+                      q % kLdsStride;
   int32_t st;
   if constexpr (Method == kMethodRkck)
     st = adjoint_system_rkck<Prob>(prm, n, i, g, T, w, dy0, dth, lds + threadIdx.x, col);
@@ -481,12 +482,15 @@ int launch_taped(const LaunchArgs* a, const TapeArgs* t, void* stream) {
     return kLaunchWorkspace;
   const TapeView T = tape_view(*t, a->n, Prob::N);
   const hipStream_t s = static_cast<hipStream_t>(stream);
+  int lanes;
+  if (spread_lanes<Prob>(a->n, &lanes) != kLaunchOk) return kLaunchHip;
+  const dim3 waves((unsigned)((a->n + lanes - 1) / lanes));
   if (a->method == kMethodRkck)
-    taped_kernel<Prob, kMethodRkck><<<dim3((unsigned)blocks), dim3(kLdsStride), 0, s>>>(
-        a->prm, a->n, a->y0, a->y1, a->g, a->ctl, a->status, a->stats, T, a->order);
+    taped_kernel<Prob, kMethodRkck><<<waves, dim3(kLdsStride), 0, s>>>(
+        a->prm, a->n, a->y0, a->y1, a->g, a->ctl, a->status, a->stats, T, a->order, lanes);
   else
-    taped_kernel<Prob, kMethodRkc><<<dim3((unsigned)blocks), dim3(kLdsStride), 0, s>>>(
-        a->prm, a->n, a->y0, a->y1, a->g, a->ctl, a->status, a->stats, T, a->order);
+    taped_kernel<Prob, kMethodRkc><<<waves, dim3(kLdsStride), 0, s>>>(
+        a->prm, a->n, a->y0, a->y1, a->g, a->ctl, a->status, a->stats, T, a->order, lanes);
   return hipGetLastError() == hipSuccess ? kLaunchOk : kLaunchHip;
 }
 
@@ -519,14 +523,17 @@ int launch_adjoint(const AdjointArgs* a, void* stream) {
   order_hist_kernel<><<<chunks, kOrderChunkThreads, 0, s>>>(keys, a->n, hist);
   order_scan_kernel<><<<1, kOrderScanThreads, 0, s>>>(hist, offs);
   order_scatter_kernel<><<<chunks, kOrderChunkThreads, 0, s>>>(keys, a->n, offs, order);
+  int lanes;
+  if (spread_lanes<Prob>(a->n, &lanes) != kLaunchOk) return kLaunchHip;
+  const dim3 waves((unsigned)((a->n + lanes - 1) / lanes));
   if (ck)
-    adjoint_kernel<Prob, kMethodRkck><<<dim3((unsigned)blocks), dim3(kLdsStride), 0, s>>>(
+    adjoint_kernel<Prob, kMethodRkck><<<waves, dim3(kLdsStride), 0, s>>>(
         a->prm, a->n, a->g, T, 0, a->w, a->dy0, a->dth, a->status, static_cast<double*>(a->ws),
-        order);
+        order, lanes);
   else
-    adjoint_kernel<Prob, kMethodRkc><<<dim3((unsigned)blocks), dim3(kLdsStride), 0, s>>>(
+    adjoint_kernel<Prob, kMethodRkc><<<waves, dim3(kLdsStride), 0, s>>>(
         a->prm, a->n, a->g, T, a->max_stages, a->w, a->dy0, a->dth, a->status,
-        static_cast<double*>(a->ws), order);
+        static_cast<double*>(a->ws), order, lanes);
   return hipGetLastError() == hipSuccess ? kLaunchOk : kLaunchHip;
 }
 

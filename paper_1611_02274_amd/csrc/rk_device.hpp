@@ -971,8 +971,20 @@ constexpr int kernel_lds_doubles() {
   return (Prob::kColumns || slot_doubles<Prob, Method>() == 0) ? 1 : slot_doubles<Prob, Method>();
 }
 
-// Plain kernel: one lane per system, system i = global thread index (the
-// paper's intDriver, Sec. 3), or order[global thread index] with an order map.
+// Position of this lane's system when a wave holds the next `lanes` systems of
+// the batch: lane l has system l mod lanes, so the lanes beyond repeat the
+// first ones.  The copies of a system take the same path and store the same
+// values; they are there because a wave whose execution mask is not full runs
+// slower here (spread_lanes).
+__device__ inline int64_t spread_position(int64_t n, int lanes) {
+  const int64_t base = (int64_t)blockIdx.x * lanes;
+  const int held = n - base < lanes ? (int)(n - base) : lanes;
+  return base + (int)threadIdx.x % held;
+}
+
+// Plain kernel: the wave's `lanes` systems (64: one lane per system, system i =
+// global thread index, the paper's intDriver, Sec. 3), through the order map if
+// there is one.
 template <class Prob, int Method, bool kPilot = false>
 __global__ __launch_bounds__(kLdsStride)
 __attribute__((amdgpu_waves_per_eu(WavesPerEu<Prob>::value))) void plain_kernel(typename Prob::Params prm, int64_t n,
@@ -983,10 +995,10 @@ __attribute__((amdgpu_waves_per_eu(WavesPerEu<Prob>::value))) void plain_kernel(
                                                            int32_t* __restrict__ stats,
                                                            double* cols,
                                                            const int32_t* __restrict__ order,
-                                                           double* __restrict__ carry) {
+                                                           double* __restrict__ carry,
+                                                           int lanes) {
   __shared__ double lds[kernel_lds_doubles<Prob, Method>() * kLdsStride];
-  const int64_t q = (int64_t)blockIdx.x * kLdsStride + threadIdx.x;
-  if (q >= n) return;
+  const int64_t q = spread_position(n, lanes);
   const int64_t i = order ? (int64_t)order[q] : q;
   integrate_system<Prob, Method>(prm, n, i, y0, y1, g, c, status, stats,
                                  lane_slot<Prob, Method>(lds, cols), carry);

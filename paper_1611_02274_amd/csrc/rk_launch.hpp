@@ -33,6 +33,30 @@ constexpr size_t block_col_bytes() {
   return Prob::kColumns ? (size_t)slot_doubles<Prob, Method>() * kLdsStride * sizeof(double) : 0;
 }
 
+// Systems per wave of a one-lane kernel over n systems: as few as still fit one
+// wave on every SIMD (64 from 256 systems per SIMD-wide row on).  A wave lasts
+// as long as its slowest system and runs every branch that one of its systems
+// takes, so a small batch is spread over the chip.  The other lanes repeat the
+// wave's systems (spread_position): with the mask left partly empty instead,
+// the same waves took 1.2x longer alone and 2.2x with one on every SIMD (van
+// der Pol, four systems a wave, 1024 waves: 0.91 against 0.36 ms; 64 waves of
+// 64 systems: 0.45 ms).  A second wave per SIMD costs more than it spreads
+// (2048 waves of two systems 0.49, 1024 of four 0.36 ms).  Systems in slot
+// columns keep 64 per wave (their workspace has a block per 64 systems).
+template <class Prob>
+int spread_lanes(int64_t n, int* lanes) {
+  *lanes = kLdsStride;
+  if (Prob::kColumns) return kLaunchOk;
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return kLaunchHip;
+  const int64_t simds = (int64_t)cus * 4;
+  const int64_t l = (n + simds - 1) / simds;
+  *lanes = (int)(l < 1 ? 1 : l > kLdsStride ? kLdsStride : l);
+  return kLaunchOk;
+}
+
 // Workgroups of the persistent grid: every resident slot the occupancy allows
 // on every compute unit of the current device, at most one per 64 systems.
 template <class Prob, int Method>
@@ -79,15 +103,20 @@ int launch_method(const LaunchArgs* a, hipStream_t s) {
       a->schedule == kSchedPersistent ||
       ((a->schedule == kSchedAuto || a->schedule == kSchedGroup) &&
        ws_bytes >= kQueueBytes + col_bytes);
-  if (!persistent) {
+  int64_t grid = 0;
+  if (persistent && persistent_grid<Prob, Method>(blocks, &grid) != kLaunchOk) return kLaunchHip;
+  if (persistent && ws_bytes < kQueueBytes + col_bytes) return kLaunchWorkspace;
+  // a grid that holds every system at once has nothing to hand out
+  if (!persistent || (!Prob::kColumns && grid == blocks)) {
     if (col_bytes && ws_bytes < kQueueBytes + (size_t)blocks * col_bytes) return kLaunchWorkspace;
-    plain_kernel<Prob, Method, kPilot><<<dim3((unsigned)blocks), dim3(kLdsStride), 0, s>>>(
-        prm, a->n, a->y0, a->y1, a->g, a->ctl, a->status, a->stats, cols, a->order, a->carry);
+    int lanes;
+    if (spread_lanes<Prob>(a->n, &lanes) != kLaunchOk) return kLaunchHip;
+    const int64_t waves = (a->n + lanes - 1) / lanes;
+    plain_kernel<Prob, Method, kPilot><<<dim3((unsigned)waves), dim3(kLdsStride), 0, s>>>(
+        prm, a->n, a->y0, a->y1, a->g, a->ctl, a->status, a->stats, cols, a->order, a->carry,
+        lanes);
     return hipGetLastError() == hipSuccess ? kLaunchOk : kLaunchHip;
   }
-  int64_t grid = 0;
-  if (persistent_grid<Prob, Method>(blocks, &grid) != kLaunchOk) return kLaunchHip;
-  if (ws_bytes < kQueueBytes + col_bytes) return kLaunchWorkspace;
   if (col_bytes) {
     // a smaller workspace runs a smaller grid
     const int64_t fit = (int64_t)((ws_bytes - kQueueBytes) / col_bytes);
