@@ -124,9 +124,10 @@ def rhs_source(net, tag: str) -> tuple[str, str]:
                 lines.append(f"    om[{int(k)}] += q;")
     body = "\n".join(lines)
     vjp = "" if columns else _vjp_source(net) + _gershgorin_source(net)
+    wide = "" if columns else _wide_source(net, body)
     group = group_source(net, tag) if columns else ""
-    fast = (f"template <>\nstruct FastVariant<gen_{tag}::Net> {{\n  using type = gen_{tag}::GNet;\n}};\n\n"
-            if columns else "")
+    fast = (f"template <>\nstruct {'FastVariant' if columns else 'SparseVariant'}<gen_{tag}::Net> "
+            f"{{\n  using type = gen_{tag}::{'GNet' if columns else 'NetR'};\n}};\n\n")
     if columns:
         launch_call = (f"rkmi::launch_with_group<rkmi::gen_{tag}::Net, rkmi::gen_{tag}::GNet>(a, s)")
         ws_call = (f"rkmi::workspace_with_group<rkmi::gen_{tag}::Net, rkmi::gen_{tag}::GNet>"
@@ -212,7 +213,7 @@ struct Net {{
     for (int k = 0; k < N; ++k) f[k] = (ld_uniform(W, k) * om[k]) * L.irho;
   }}
 {vjp}}};
-{group}
+{wide}{group}
 }}  // namespace gen_{tag}
 
 {fast}}}  // namespace rkmi
@@ -234,6 +235,74 @@ extern "C" int64_t rkmi_gen_{tag}_workspace(int method, int schedule, int64_t n)
 }}
 {"" if columns else _adjoint_exports(tag)}"""
     return header, source
+
+
+def _registers(body: str) -> str:
+    """A generated evaluation with the rate constants taken from the lane's
+    registers."""
+    import re
+    body = re.sub(r"kf = L\.kf\[z \+ (\d+) \* kLdsStride\];", r"kf = L.kf[\1];", body)
+    return re.sub(r"kr = kf \* ld_uniform\(iK, (\d+)\);", r"kr = L.kr[\1];", body)
+
+
+def _wide_source(net, body: str) -> str:
+    """The network with both rate constants of every reaction in registers,
+    compiled for one wave per SIMD: batches that do not put a second wave on a
+    SIMD (rk_device.hpp SparseVariant)."""
+    return f"""
+// The same network for batches of at most one wave per SIMD: such a wave has
+// the SIMD's registers to itself and nothing to hide latency behind, so both
+// rate constants of every reaction stay in registers (no LDS read of k_f, no
+// scalar load of 1/K, no k_r product per evaluation).  9 species RKC, 300 systems
+// 21.5 -> 16.4 ms, RKCK 5001 13.4 -> 10.2 ms; 13 species RKC 65536 systems 13.8 ->
+// 12.1 ms, its reverse sweep 2^16 systems 23.3 -> 22.2 ms.  The RKCK reverse
+// sweep holds six stages' arguments and adjoints: 9 species gain (65536 forward
+// and back 91.9 -> 84.7 ms), at 13 the constants do not fit (216 registers
+// spilled, 15.3 -> 18.6 ms).
+struct NetR {{
+  static constexpr int N = Net::N;
+  static constexpr int NR = Net::NR;
+  static constexpr bool kColumns = false;
+  static constexpr int kGroupLanes = 1;
+  static constexpr int kLaneDoubles = NR;   // set-up only
+  static constexpr int kWavesPerEu = 1;
+  static constexpr bool kSweepRkck = {"true" if 3 * net.n_rx + 6 * net.n_sp <= 128 else "false"};
+  using Params = Net::Params;
+  struct Lane {{
+    double kf[NR], kr[NR];
+    double rho, irho;
+  }};
+  RKMI_HD static void init(Lane& L, const Params& p, const double* __restrict__ g, int64_t i,
+                           int64_t n, double* slot) {{
+    Net::Lane s;
+    Net::init(s, p, g, i, n, slot);
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {{
+      L.kf[j] = slot[j * kLdsStride];
+      L.kr[j] = L.kf[j] * ld_uniform(p, 3 * NR + j);
+    }}
+    L.rho = s.rho;
+    L.irho = s.irho;
+  }}
+  template <class VI, class VO>
+  RKMI_HD static void rhs(const Lane& L, const Params& p, const VI& y, VO& f) {{
+    const double* __restrict__ W = p + 4 * NR;
+    const double* __restrict__ iW = W + N;
+    double C[N], om[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) C[k] = (L.rho * y[k]) * ld_uniform(iW, k);
+    double M = 0.0;
+#pragma unroll
+    for (int k = 0; k < N; ++k) M += C[k];
+#pragma unroll
+    for (int k = 0; k < N; ++k) om[k] = 0.0;
+    double q, kf, kr;
+{_registers(body)}
+#pragma unroll
+    for (int k = 0; k < N; ++k) f[k] = (ld_uniform(W, k) * om[k]) * L.irho;
+  }}
+{_registers(_vjp_source(net))}}};
+"""
 
 
 def thermal_source(net, tag: str) -> tuple[str, str]:

@@ -471,6 +471,16 @@ __global__ void adjoint_keys_kernel(const int32_t* __restrict__ count, int64_t n
   keys[(int64_t)kStReject * n + i] = 0;
 }
 
+// Whether a sparse variant also runs the RKCK reverse sweep (kSweepRkck).
+template <class P, class = void>
+struct SparseSweepRkck {
+  static constexpr bool value = true;
+};
+template <class P>
+struct SparseSweepRkck<P, std::void_t<decltype(P::kSweepRkck)>> {
+  static constexpr bool value = P::kSweepRkck;
+};
+
 template <class Prob>
 int launch_taped(const LaunchArgs* a, const TapeArgs* t, void* stream) {
   static_assert(!Prob::kColumns, "the adjoint keeps the system's vectors in registers");
@@ -483,14 +493,18 @@ int launch_taped(const LaunchArgs* a, const TapeArgs* t, void* stream) {
   const TapeView T = tape_view(*t, a->n, Prob::N);
   const hipStream_t s = static_cast<hipStream_t>(stream);
   int lanes;
-  if (spread_lanes<Prob>(a->n, &lanes) != kLaunchOk) return kLaunchHip;
+  bool sparse;
+  if (spread_lanes<Prob>(a->n, &lanes, &sparse) != kLaunchOk) return kLaunchHip;
   const dim3 waves((unsigned)((a->n + lanes - 1) / lanes));
+  const auto run = [&](auto kernel) {
+    kernel<<<waves, dim3(kLdsStride), 0, s>>>(a->prm, a->n, a->y0, a->y1, a->g, a->ctl, a->status,
+                                              a->stats, T, a->order, lanes);
+  };
+  using Sparse = typename SparseVariant<Prob>::type;
   if (a->method == kMethodRkck)
-    taped_kernel<Prob, kMethodRkck><<<waves, dim3(kLdsStride), 0, s>>>(
-        a->prm, a->n, a->y0, a->y1, a->g, a->ctl, a->status, a->stats, T, a->order, lanes);
+    sparse ? run(taped_kernel<Sparse, kMethodRkck>) : run(taped_kernel<Prob, kMethodRkck>);
   else
-    taped_kernel<Prob, kMethodRkc><<<waves, dim3(kLdsStride), 0, s>>>(
-        a->prm, a->n, a->y0, a->y1, a->g, a->ctl, a->status, a->stats, T, a->order, lanes);
+    sparse ? run(taped_kernel<Sparse, kMethodRkc>) : run(taped_kernel<Prob, kMethodRkc>);
   return hipGetLastError() == hipSuccess ? kLaunchOk : kLaunchHip;
 }
 
@@ -524,16 +538,22 @@ int launch_adjoint(const AdjointArgs* a, void* stream) {
   order_scan_kernel<><<<1, kOrderScanThreads, 0, s>>>(hist, offs);
   order_scatter_kernel<><<<chunks, kOrderChunkThreads, 0, s>>>(keys, a->n, offs, order);
   int lanes;
-  if (spread_lanes<Prob>(a->n, &lanes) != kLaunchOk) return kLaunchHip;
+  bool sparse;
+  if (spread_lanes<Prob>(a->n, &lanes, &sparse) != kLaunchOk) return kLaunchHip;
   const dim3 waves((unsigned)((a->n + lanes - 1) / lanes));
+  const auto run = [&](auto kernel) {
+    kernel<<<waves, dim3(kLdsStride), 0, s>>>(a->prm, a->n, a->g, T, ck ? 0 : a->max_stages, a->w,
+                                              a->dy0, a->dth, a->status,
+                                              static_cast<double*>(a->ws), order, lanes);
+  };
+  using Sparse = typename SparseVariant<Prob>::type;
+  // (a sparse variant that does not fit the RKCK sweep's registers leaves it to
+  // the network itself)
+  using SparseCk = typename std::conditional<SparseSweepRkck<Sparse>::value, Sparse, Prob>::type;
   if (ck)
-    adjoint_kernel<Prob, kMethodRkck><<<waves, dim3(kLdsStride), 0, s>>>(
-        a->prm, a->n, a->g, T, 0, a->w, a->dy0, a->dth, a->status, static_cast<double*>(a->ws),
-        order, lanes);
+    sparse ? run(adjoint_kernel<SparseCk, kMethodRkck>) : run(adjoint_kernel<Prob, kMethodRkck>);
   else
-    adjoint_kernel<Prob, kMethodRkc><<<waves, dim3(kLdsStride), 0, s>>>(
-        a->prm, a->n, a->g, T, a->max_stages, a->w, a->dy0, a->dth, a->status,
-        static_cast<double*>(a->ws), order, lanes);
+    sparse ? run(adjoint_kernel<Sparse, kMethodRkc>) : run(adjoint_kernel<Prob, kMethodRkc>);
   return hipGetLastError() == hipSuccess ? kLaunchOk : kLaunchHip;
 }
 

@@ -101,6 +101,13 @@ struct WavesPerEu<P, std::void_t<decltype(P::kWavesPerEu)>> {
   static constexpr int value = P::kWavesPerEu;
 };
 
+// The variant of a problem that runs batches of at most one wave per SIMD: the
+// problem itself, or the one generated for them.
+template <class P>
+struct SparseVariant {
+  using type = P;
+};
+
 // Controller state carried from one call to the next instead of the restart
 // (Sec. 3 mentions the alternative): rows of a [kCarryRows + N][n] array, the
 // RKC eigenvector estimate in the last N rows; RKCK uses kCarryValid and

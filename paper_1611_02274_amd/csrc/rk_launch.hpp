@@ -43,9 +43,11 @@ constexpr size_t block_col_bytes() {
 // 64 systems: 0.45 ms).  A second wave per SIMD costs more than it spreads
 // (2048 waves of two systems 0.49, 1024 of four 0.36 ms).  Systems in slot
 // columns keep 64 per wave (their workspace has a block per 64 systems).
+// *sparse: at most one wave per SIMD (the SparseVariant's case).
 template <class Prob>
-int spread_lanes(int64_t n, int* lanes) {
+int spread_lanes(int64_t n, int* lanes, bool* sparse) {
   *lanes = kLdsStride;
+  *sparse = false;
   if (Prob::kColumns) return kLaunchOk;
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
@@ -54,6 +56,7 @@ int spread_lanes(int64_t n, int* lanes) {
   const int64_t simds = (int64_t)cus * 4;
   const int64_t l = (n + simds - 1) / simds;
   *lanes = (int)(l < 1 ? 1 : l > kLdsStride ? kLdsStride : l);
+  *sparse = l <= kLdsStride;
   return kLaunchOk;
 }
 
@@ -110,11 +113,17 @@ int launch_method(const LaunchArgs* a, hipStream_t s) {
   if (!persistent || (!Prob::kColumns && grid == blocks)) {
     if (col_bytes && ws_bytes < kQueueBytes + (size_t)blocks * col_bytes) return kLaunchWorkspace;
     int lanes;
-    if (spread_lanes<Prob>(a->n, &lanes) != kLaunchOk) return kLaunchHip;
-    const int64_t waves = (a->n + lanes - 1) / lanes;
-    plain_kernel<Prob, Method, kPilot><<<dim3((unsigned)waves), dim3(kLdsStride), 0, s>>>(
-        prm, a->n, a->y0, a->y1, a->g, a->ctl, a->status, a->stats, cols, a->order, a->carry,
-        lanes);
+    bool sparse;
+    if (spread_lanes<Prob>(a->n, &lanes, &sparse) != kLaunchOk) return kLaunchHip;
+    const dim3 waves((unsigned)((a->n + lanes - 1) / lanes));
+    if (sparse)
+      plain_kernel<typename SparseVariant<Prob>::type, Method, kPilot>
+          <<<waves, dim3(kLdsStride), 0, s>>>(prm, a->n, a->y0, a->y1, a->g, a->ctl, a->status,
+                                              a->stats, cols, a->order, a->carry, lanes);
+    else
+      plain_kernel<Prob, Method, kPilot><<<waves, dim3(kLdsStride), 0, s>>>(
+          prm, a->n, a->y0, a->y1, a->g, a->ctl, a->status, a->stats, cols, a->order, a->carry,
+          lanes);
     return hipGetLastError() == hipSuccess ? kLaunchOk : kLaunchHip;
   }
   if (col_bytes) {
