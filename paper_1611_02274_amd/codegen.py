@@ -125,11 +125,12 @@ def rhs_source(net, tag: str) -> tuple[str, str]:
     body = "\n".join(lines)
     vjp = "" if columns else _vjp_source(net) + _gershgorin_source(net)
     wide = "" if columns else _wide_source(net, body)
-    group = group_source(net, tag) if columns else ""
+    group = group_source(net, tag) + wide_source(net, tag) if columns else ""
     fast = (f"template <>\nstruct {'FastVariant' if columns else 'SparseVariant'}<gen_{tag}::Net> "
             f"{{\n  using type = gen_{tag}::{'GNet' if columns else 'NetR'};\n}};\n\n")
     if columns:
-        launch_call = (f"rkmi::launch_with_group<rkmi::gen_{tag}::Net, rkmi::gen_{tag}::GNet>(a, s)")
+        launch_call = (f"rkmi::launch_with_wide<rkmi::gen_{tag}::Net, rkmi::gen_{tag}::GNet, "
+                       f"rkmi::gen_{tag}::WNet>(a, s)")
         ws_call = (f"rkmi::workspace_with_group<rkmi::gen_{tag}::Net, rkmi::gen_{tag}::GNet>"
                    "(method, schedule, n)")
     else:
@@ -793,6 +794,125 @@ struct GNet {{
     L.irho = 1.0 / rho;
     L.bnd = kBnd[x.r];
     if (x.r == 0) Q[kSentinel] = 0.0;
+  }}
+}};
+"""
+
+
+def wide_lanes(n_sp: int) -> int:
+    """Lanes per system of the wide variant: one species to a lane."""
+    return 32 if n_sp <= 32 else 64
+
+
+def _wide_layout(net, L):
+    """The wide layout of a network (rk_group.hpp group_rhs_wide): lane r owns
+    species sp[r], forms the rates at positions m L + r and adds its species'
+    signed rates.  LDS area of a system (doubles): C [0, N), the place of
+    lanes without a species at N + 1 | +q | the zero | scratch | -q, with -q a
+    multiple of 64 behind +q (one instruction stores both)."""
+    n, nr = net.n_sp, net.n_rx
+    assert n <= L
+    R = -(-nr // L)
+    pos_of, rx_of, m_first = _group_positions(net, L, R)
+    off_q = n + 2 + (n % 2)
+    off_zero = off_q + R * L
+    off_red = off_zero + 1 + (off_zero + 1) % 2
+    neg = -(-(off_red + n - off_q) // 64) * 64
+    lds = off_q + neg + R * L
+    lds += lds % 2
+    ops = []                     # [L][R][4] LDS byte offsets; [M]: byte offset of C_N
+    for r in range(L):
+        for m in range(R):
+            j = rx_of[m * L + r]
+            a, b = (int(net.reac[j][0]), int(net.reac[j][1])) if j >= 0 else (0, 0)
+            c, d = (int(net.prod[j][0]), int(net.prod[j][1])) if j >= 0 else (0, 0)
+            ops += [8 * (n if k < 0 else k) for k in (a, b, c, d)]
+    terms = [[8 * (off_q + pos_of[c >> 1] + neg * (c & 1)) for c in lst]
+             for lst in _species_terms(net)]
+    T = max(len(t) for t in terms)
+    T += (-T) % 4
+    tm = []                      # [L][T]
+    for r in range(L):
+        lst = terms[r] if r < n else []
+        tm += lst + [8 * off_zero] * (T - len(lst))
+    return dict(n=n, nr=nr, L=L, R=R, m_first=m_first, off_q=off_q, off_zero=off_zero,
+                off_red=off_red, neg=neg, lds=lds, ops=ops, tm=tm, T=T, rx_of=rx_of)
+
+
+def wide_source(net, tag: str) -> str:
+    """The wide variant of a network: one species per lane, for small batches."""
+    n = net.n_sp
+    G = _wide_layout(net, wide_lanes(n))
+    return f"""
+// Wide variant: {G["L"]} lanes per system, one species per lane (rk_group.hpp).
+struct WNet {{
+  static constexpr bool kWide = true;
+  // largest batches it runs, in systems per SIMD (rk_group.hpp group_rhs_wide)
+  static constexpr int kMaxRkck = {64 if n <= 32 else 32};
+  static constexpr int kMaxRkc = {16 if n <= 32 else 2};
+  static constexpr int N = {n};
+  static constexpr int NR = {G["nr"]};
+  static constexpr int kL = {G["L"]};
+  static constexpr int kGroupLanes = {G["L"]};
+  static constexpr bool kColumns = false;
+  static constexpr int kLaneDoubles = 0;
+  static constexpr int kWavesPerEuRkc = {2 if n <= 32 else 1};
+  static constexpr int kWavesPerEuRkck = 2;
+  static constexpr int S = 1;
+  static constexpr int R = {G["R"]};
+  static constexpr int kMSlot = {G["m_first"]};   // first slot that may hold a [M] reaction
+  static constexpr int kOffC = 0;
+  static constexpr int kOffQ = {G["off_q"]};
+  static constexpr int kOffZero = {G["off_zero"]};
+  static constexpr int kNegOff = {G["neg"]};
+  static constexpr int kOffRed = {G["off_red"]};
+  static constexpr int kLdsPerSystem = {G["lds"]};
+  static constexpr int kTermLen = {G["T"]};
+  using Params = const double*;
+{_table("kSp", "int", [r if r < n else -1 for r in range(G["L"])])}
+{_table("kRxOf", "int16_t", G["rx_of"])}
+  // LDS byte offsets within the system's area: each lane's rate operands
+  // (R x 4), and the signed rates of its species in reaction order
+{_table("kOp", "uint16_t", G["ops"], align=16)}
+{_table("kTm", "uint16_t", G["tm"], align=16)}
+  struct Lane {{
+    double kf[R], kr[R];
+    double W[S], iW[S];
+    double rho, irho;
+    uint32_t op[R][4], tm[kTermLen];   // LDS addresses, formed once per system
+    uint32_t c_at;
+  }};
+  __device__ __attribute__((noinline)) static void rates(Params p, double T, double* lds, int r) {{
+    const double lnT = crm::cr_log(T);
+    double* const Q = lds + kOffQ;
+#pragma nounroll
+    for (int m = 0; m < R; ++m) {{
+      const int j = kRxOf[m * kL + r];
+      Q[m * kL + r] = j >= 0 ? crm::cr_exp(p[j] + p[NR + j] * lnT - p[2 * NR + j] / T) : 0.0;
+    }}
+  }}
+  __device__ static void init(Lane& L, const Params& p, const double* __restrict__ g, int64_t i,
+                              int64_t n, const Grp<WNet>& x) {{
+    double* const Q = x.lds + kOffQ;
+    rates(p, g[i], x.lds, x.r);
+#pragma unroll
+    for (int m = 0; m < R; ++m) {{
+      const int j = kRxOf[m * kL + x.r];
+      L.kf[m] = Q[m * kL + x.r];
+      L.kr[m] = j >= 0 ? L.kf[m] * p[3 * NR + j] : 0.0;
+    }}
+    const int k = x.sp[0];
+    L.W[0] = k >= 0 ? p[4 * NR + k] : 0.0;
+    L.iW[0] = k >= 0 ? p[4 * NR + N + k] : 0.0;
+    L.rho = g[n + i];
+    L.irho = 1.0 / L.rho;
+    const uint32_t base = lds_address(x.lds);
+    L.c_at = base + 8 * (k >= 0 ? k : N + 1);
+#pragma unroll
+    for (int q = 0; q < 4 * R; ++q) L.op[q / 4][q % 4] = base + kOp[x.r * 4 * R + q];
+#pragma unroll
+    for (int t = 0; t < kTermLen; ++t) L.tm[t] = base + kTm[x.r * kTermLen + t];
+    if (x.r == 0) x.lds[kOffZero] = 0.0;
   }}
 }};
 """

@@ -3,7 +3,7 @@
 #include "net_n32r133_bcb31e07.hpp"
 
 extern "C" int rkmi_gen_n32r133_bcb31e07_launch(const rkmi::LaunchArgs* a, void* s) {
-  return rkmi::launch_with_group<rkmi::gen_n32r133_bcb31e07::Net, rkmi::gen_n32r133_bcb31e07::GNet>(a, s);
+  return rkmi::launch_with_wide<rkmi::gen_n32r133_bcb31e07::Net, rkmi::gen_n32r133_bcb31e07::GNet, rkmi::gen_n32r133_bcb31e07::WNet>(a, s);
 }
 
 extern "C" int rkmi_gen_n32r133_bcb31e07_host(const rkmi::LaunchArgs* a) {

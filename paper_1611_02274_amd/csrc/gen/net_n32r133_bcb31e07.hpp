@@ -1090,6 +1090,186 @@ struct GNet {
   }
 };
 
+// Wide variant: 32 lanes per system, one species per lane (rk_group.hpp).
+struct WNet {
+  static constexpr bool kWide = true;
+  // largest batches it runs, in systems per SIMD (rk_group.hpp group_rhs_wide)
+  static constexpr int kMaxRkck = 64;
+  static constexpr int kMaxRkc = 16;
+  static constexpr int N = 32;
+  static constexpr int NR = 133;
+  static constexpr int kL = 32;
+  static constexpr int kGroupLanes = 32;
+  static constexpr bool kColumns = false;
+  static constexpr int kLaneDoubles = 0;
+  static constexpr int kWavesPerEuRkc = 2;
+  static constexpr int kWavesPerEuRkck = 2;
+  static constexpr int S = 1;
+  static constexpr int R = 5;
+  static constexpr int kMSlot = 4;   // first slot that may hold a [M] reaction
+  static constexpr int kOffC = 0;
+  static constexpr int kOffQ = 34;
+  static constexpr int kOffZero = 194;
+  static constexpr int kNegOff = 256;
+  static constexpr int kOffRed = 196;
+  static constexpr int kLdsPerSystem = 450;
+  static constexpr int kTermLen = 28;
+  using Params = const double*;
+  static constexpr int kSp[32] = {
+      0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15,
+      16, 17, 18, 19, 20, 21, 22, 23, 24, 25, 26, 27, 28, 29, 30, 31};
+  static constexpr int16_t kRxOf[160] = {
+      0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15,
+      16, 19, 20, 21, 22, 23, 24, 26, 27, 28, 29, 30, 31, 32, 33, 34,
+      35, 36, 37, 38, 39, 40, 41, 42, 43, 44, 45, 46, 47, 48, 49, 50,
+      51, 52, 53, 54, 55, 56, 57, 59, 60, 61, 62, 63, 64, 65, 67, 68,
+      69, 70, 71, 72, 73, 74, 75, 76, 78, 80, 81, 82, 83, 84, 85, 87,
+      89, 91, 92, 93, 94, 95, 96, 97, 98, 99, 100, 101, 102, 103, 104, 105,
+      106, 107, 108, 109, 110, 111, 112, 115, 117, 118, 119, 120, 121, 122, 123, 124,
+      125, 126, 127, 128, 129, 130, 131, 132, -1, -1, -1, -1, -1, -1, -1, -1,
+      17, 18, 25, 58, 66, 77, 79, 86, 88, 90, 113, 114, 116, -1, -1, -1,
+      -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1};
+  // LDS byte offsets within the system's area: each lane's rate operands
+  // (R x 4), and the signed rates of its species in reaction order
+  alignas(16) static constexpr uint16_t kOp[640] = {
+      64, 120, 32, 184, 16, 208, 104, 248, 32, 56, 160, 224, 24, 32, 0, 112,
+      16, 16, 88, 256, 120, 240, 48, 56, 24, 176, 112, 112, 24, 208, 72, 88,
+      112, 240, 16, 216, 216, 256, 48, 168, 96, 224, 136, 136, 128, 208, 48, 96,
+      112, 184, 120, 136, 136, 192, 40, 144, 176, 256, 24, 112, 176, 184, 32, 216,
+      8, 208, 128, 128, 24, 248, 16, 224, 128, 240, 80, 200, 24, 208, 96, 256,
+      72, 200, 184, 216, 40, 104, 80, 176, 64, 208, 136, 200, 88, 104, 80, 232,
+      16, 200, 208, 256, 48, 168, 112, 152, 16, 224, 112, 120, 8, 168, 32, 128,
+      8, 128, 48, 160, 128, 256, 0, 80, 80, 168, 24, 208, 104, 224, 152, 192,
+      32, 240, 24, 200, 120, 160, 8, 248, 64, 256, 0, 56, 24, 208, 104, 224,
+      208, 216, 96, 200, 56, 176, 112, 136, 88, 248, 8, 192, 112, 240, 96, 256,
+      208, 224, 168, 200, 128, 192, 80, 176, 96, 240, 208, 208, 168, 216, 96, 224,
+      224, 256, 32, 120, 64, 168, 40, 72, 80, 248, 128, 160, 112, 240, 104, 224,
+      8, 208, 56, 80, 248, 256, 0, 160, 88, 112, 16, 192, 32, 240, 8, 136,
+      32, 32, 0, 40, 8, 136, 56, 160, 32, 128, 136, 256, 72, 128, 56, 200,
+      144, 152, 48, 96, 72, 160, 64, 128, 0, 216, 40, 152, 240, 256, 8, 128,
+      72, 192, 144, 224, 24, 56, 16, 64, 48, 136, 240, 248, 32, 208, 152, 176,
+      96, 256, 152, 192, 88, 136, 40, 104, 80, 168, 112, 240, 40, 128, 160, 168,
+      96, 112, 176, 208, 0, 0, 0, 0, 8, 176, 16, 168, 32, 128, 160, 248,
+      96, 112, 144, 168, 176, 200, 112, 216, 0, 0, 0, 0, 128, 168, 112, 200,
+      152, 176, 112, 200, 128, 136, 96, 120, 32, 208, 40, 240, 0, 0, 0, 0,
+      56, 160, 80, 224, 8, 216, 48, 136, 16, 80, 48, 88, 136, 160, 152, 176,
+      0, 0, 0, 0, 128, 168, 136, 160, 40, 112, 32, 176, 40, 200, 72, 112,
+      80, 136, 160, 208, 0, 0, 0, 0, 192, 248, 160, 176, 112, 184, 64, 160,
+      160, 160, 48, 112, 200, 224, 72, 248, 0, 0, 0, 0, 160, 168, 24, 136,
+      160, 216, 168, 240, 128, 192, 24, 144, 56, 224, 64, 248, 0, 0, 0, 0,
+      72, 232, 144, 160, 176, 240, 144, 248, 136, 184, 64, 200, 24, 72, 40, 152,
+      0, 0, 0, 0, 80, 224, 112, 152, 24, 216, 136, 160, 72, 192, 32, 96,
+      128, 176, 56, 192, 0, 0, 0, 0, 32, 136, 40, 56, 40, 96, 176, 216,
+      16, 72, 8, 136, 80, 224, 24, 200, 0, 0, 0, 0, 192, 216, 96, 112,
+      120, 176, 40, 160, 24, 128, 160, 160, 176, 248, 192, 224, 0, 0, 0, 0,
+      0, 208, 16, 72, 160, 248, 24, 56, 16, 40, 0, 192, 0, 0, 0, 0,
+      0, 0, 0, 0, 8, 72, 120, 200, 120, 160, 32, 48, 16, 160, 88, 120,
+      0, 0, 0, 0, 0, 0, 0, 0, 72, 120, 152, 224, 184, 240, 152, 200,
+      112, 152, 16, 72, 0, 0, 0, 0, 0, 0, 0, 0, 160, 208, 64, 104,
+      200, 200, 72, 240, 64, 232, 24, 144, 0, 0, 0, 0, 0, 0, 0, 0,
+      184, 248, 152, 224, 120, 168, 24, 64, 40, 80, 48, 176, 0, 0, 0, 0,
+      0, 0, 0, 0, 80, 168, 120, 144, 224, 248, 32, 64, 24, 120, 8, 32,
+      0, 0, 0, 0, 0, 0, 0, 0, 112, 200, 184, 192, 56, 88, 32, 104,
+      88, 200, 16, 208, 0, 0, 0, 0, 0, 0, 0, 0, 48, 144, 56, 104,
+      72, 232, 104, 168, 112, 168, 192, 224, 0, 0, 0, 0, 0, 0, 0, 0};
+  alignas(16) static constexpr uint16_t kTm[896] = {
+      2512, 1336, 1344, 864, 1368, 976, 1040, 3176, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552,
+      1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 2432, 2520, 2600, 608,
+      2704, 2872, 960, 1016, 3128, 1088, 1384, 1096, 3160, 3168, 1552, 1552, 1552, 1552, 1552, 1552,
+      1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 352, 384, 3344, 3344, 464, 2576, 2616, 624,
+      3376, 808, 2960, 3008, 3024, 3032, 992, 1024, 1048, 1552, 1552, 1552, 1552, 1552, 1552, 1552,
+      1552, 1552, 1552, 1552, 320, 2376, 424, 1312, 2584, 2672, 2744, 3368, 720, 752, 2840, 2856,
+      832, 936, 3016, 1000, 3064, 3088, 3248, 1216, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552,
+      272, 296, 2496, 2656, 2688, 664, 728, 760, 768, 2832, 824, 2880, 2912, 2912, 1360, 952,
+      1016, 3088, 3424, 3184, 3208, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 344, 376, 448, 2608,
+      2712, 2752, 712, 864, 2936, 2968, 3024, 3056, 1056, 1128, 1160, 1200, 1552, 1552, 1552, 1552,
+      1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 280, 2360, 1304, 2568, 544, 616, 656, 728,
+      2928, 912, 928, 1008, 1080, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552,
+      1552, 1552, 1552, 1552, 280, 360, 2448, 448, 520, 2672, 720, 2816, 2832, 2888, 1344, 1112,
+      1120, 3240, 1208, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552,
+      2320, 2392, 488, 624, 672, 752, 760, 2864, 3392, 872, 944, 3048, 1192, 1552, 1552, 1552,
+      1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 2352, 344, 2408, 2416,
+      2480, 464, 2520, 2528, 744, 2824, 792, 2920, 920, 3000, 3008, 992, 1184, 3248, 1552, 1552,
+      1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 2368, 400, 2488, 2552, 560, 592, 2648, 2680,
+      1336, 2960, 3056, 1064, 1072, 1112, 3224, 3264, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552,
+      1552, 1552, 1552, 1552, 2400, 2424, 1296, 2816, 792, 912, 984, 3072, 3120, 3144, 1552, 1552,
+      1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552,
+      2336, 456, 544, 584, 616, 2752, 1320, 2896, 2944, 1352, 904, 952, 3440, 1104, 3192, 1552,
+      1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 328, 376, 488, 520,
+      528, 2608, 2624, 768, 776, 856, 3120, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552,
+      1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 312, 2400, 392, 440, 1312, 456, 2560, 536,
+      536, 568, 632, 648, 2712, 2720, 2848, 840, 2904, 2944, 3400, 920, 928, 3040, 3080, 1040,
+      3096, 3192, 1152, 1552, 2320, 2328, 472, 2528, 504, 568, 2760, 2776, 2800, 800, 904, 1360,
+      984, 3064, 3136, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552,
+      2408, 2440, 2456, 2592, 552, 552, 2640, 600, 2688, 824, 3384, 872, 2936, 2952, 2984, 3016,
+      3112, 3128, 3424, 1384, 3256, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 288, 288, 2424, 408,
+      424, 2496, 608, 656, 696, 800, 816, 840, 2928, 2952, 2992, 960, 3104, 1376, 3168, 3216,
+      3224, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 368, 432, 504, 2568, 2664, 688, 896, 936,
+      1000, 1056, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552,
+      1552, 1552, 1552, 1552, 312, 440, 480, 496, 576, 2664, 2696, 736, 3040, 1392, 1128, 1136,
+      1168, 1200, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552,
+      2448, 408, 416, 2472, 432, 2536, 600, 640, 672, 2728, 696, 712, 2768, 2776, 784, 2920,
+      888, 1368, 2976, 2976, 968, 968, 3032, 1080, 3136, 1120, 3216, 1176, 2360, 2368, 336, 2392,
+      384, 2440, 1304, 2456, 2472, 2552, 2680, 680, 2800, 776, 2872, 888, 896, 3080, 3152, 1552,
+      1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 2344, 2432, 416, 3360, 2584, 560, 592, 2696,
+      664, 2736, 704, 2760, 2888, 1008, 1136, 1144, 3200, 1168, 3256, 3272, 1552, 1552, 1552, 1552,
+      1552, 1552, 1552, 1552, 272, 2344, 304, 2544, 512, 2720, 2784, 2848, 2992, 1552, 1552, 1552,
+      1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552,
+      352, 2416, 2464, 2504, 512, 576, 2640, 2984, 3000, 976, 1032, 3104, 1096, 1392, 1208, 1224,
+      1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 2352, 336, 360, 392,
+      472, 2560, 584, 648, 736, 2792, 2792, 3376, 816, 832, 2968, 944, 3072, 1064, 3200, 3232,
+      1216, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 320, 2376, 2384, 2512, 2536, 2576, 2592, 2600,
+      2632, 3368, 1328, 2840, 2864, 848, 848, 1024, 3160, 3184, 1144, 3208, 1176, 1552, 1552, 1552,
+      1552, 1552, 1552, 1552, 296, 304, 3352, 2504, 2632, 2704, 2728, 2744, 704, 1048, 3152, 3176,
+      1152, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552,
+      2336, 328, 2384, 368, 400, 2488, 480, 496, 2616, 2624, 2808, 784, 808, 856, 3408, 1032,
+      1104, 3232, 3240, 3264, 1224, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 2480, 2824, 3048, 1072,
+      1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552,
+      1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 2328, 2656, 632, 680, 2736, 2784, 744, 2880,
+      2896, 2904, 880, 3400, 3096, 3112, 3432, 1160, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552,
+      1552, 1552, 1552, 1552, 2464, 2544, 528, 2648, 640, 688, 2768, 2808, 2856, 880, 3416, 1088,
+      3144, 1184, 1192, 3272, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552, 1552};
+  struct Lane {
+    double kf[R], kr[R];
+    double W[S], iW[S];
+    double rho, irho;
+    uint32_t op[R][4], tm[kTermLen];   // LDS addresses, formed once per system
+    uint32_t c_at;
+  };
+  __device__ __attribute__((noinline)) static void rates(Params p, double T, double* lds, int r) {
+    const double lnT = crm::cr_log(T);
+    double* const Q = lds + kOffQ;
+#pragma nounroll
+    for (int m = 0; m < R; ++m) {
+      const int j = kRxOf[m * kL + r];
+      Q[m * kL + r] = j >= 0 ? crm::cr_exp(p[j] + p[NR + j] * lnT - p[2 * NR + j] / T) : 0.0;
+    }
+  }
+  __device__ static void init(Lane& L, const Params& p, const double* __restrict__ g, int64_t i,
+                              int64_t n, const Grp<WNet>& x) {
+    double* const Q = x.lds + kOffQ;
+    rates(p, g[i], x.lds, x.r);
+#pragma unroll
+    for (int m = 0; m < R; ++m) {
+      const int j = kRxOf[m * kL + x.r];
+      L.kf[m] = Q[m * kL + x.r];
+      L.kr[m] = j >= 0 ? L.kf[m] * p[3 * NR + j] : 0.0;
+    }
+    const int k = x.sp[0];
+    L.W[0] = k >= 0 ? p[4 * NR + k] : 0.0;
+    L.iW[0] = k >= 0 ? p[4 * NR + N + k] : 0.0;
+    L.rho = g[n + i];
+    L.irho = 1.0 / L.rho;
+    const uint32_t base = lds_address(x.lds);
+    L.c_at = base + 8 * (k >= 0 ? k : N + 1);
+#pragma unroll
+    for (int q = 0; q < 4 * R; ++q) L.op[q / 4][q % 4] = base + kOp[x.r * 4 * R + q];
+#pragma unroll
+    for (int t = 0; t < kTermLen; ++t) L.tm[t] = base + kTm[x.r * kTermLen + t];
+    if (x.r == 0) x.lds[kOffZero] = 0.0;
+  }
+};
+
 }  // namespace gen_n32r133_bcb31e07
 
 template <>

@@ -3,7 +3,7 @@
 #include "net_n53r325_7a51609a.hpp"
 
 extern "C" int rkmi_gen_n53r325_7a51609a_launch(const rkmi::LaunchArgs* a, void* s) {
-  return rkmi::launch_with_group<rkmi::gen_n53r325_7a51609a::Net, rkmi::gen_n53r325_7a51609a::GNet>(a, s);
+  return rkmi::launch_with_wide<rkmi::gen_n53r325_7a51609a::Net, rkmi::gen_n53r325_7a51609a::GNet, rkmi::gen_n53r325_7a51609a::WNet>(a, s);
 }
 
 extern "C" int rkmi_gen_n53r325_7a51609a_host(const rkmi::LaunchArgs* a) {

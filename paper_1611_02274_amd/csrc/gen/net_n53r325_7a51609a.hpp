@@ -2474,6 +2474,378 @@ struct GNet {
   }
 };
 
+// Wide variant: 64 lanes per system, one species per lane (rk_group.hpp).
+struct WNet {
+  static constexpr bool kWide = true;
+  // largest batches it runs, in systems per SIMD (rk_group.hpp group_rhs_wide)
+  static constexpr int kMaxRkck = 32;
+  static constexpr int kMaxRkc = 2;
+  static constexpr int N = 53;
+  static constexpr int NR = 325;
+  static constexpr int kL = 64;
+  static constexpr int kGroupLanes = 64;
+  static constexpr bool kColumns = false;
+  static constexpr int kLaneDoubles = 0;
+  static constexpr int kWavesPerEuRkc = 1;
+  static constexpr int kWavesPerEuRkck = 2;
+  static constexpr int S = 1;
+  static constexpr int R = 6;
+  static constexpr int kMSlot = 5;   // first slot that may hold a [M] reaction
+  static constexpr int kOffC = 0;
+  static constexpr int kOffQ = 56;
+  static constexpr int kOffZero = 440;
+  static constexpr int kNegOff = 448;
+  static constexpr int kOffRed = 442;
+  static constexpr int kLdsPerSystem = 888;
+  static constexpr int kTermLen = 44;
+  using Params = const double*;
+  static constexpr int kSp[64] = {
+      0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15,
+      16, 17, 18, 19, 20, 21, 22, 23, 24, 25, 26, 27, 28, 29, 30, 31,
+      32, 33, 34, 35, 36, 37, 38, 39, 40, 41, 42, 43, 44, 45, 46, 47,
+      48, 49, 50, 51, 52, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1};
+  static constexpr int16_t kRxOf[384] = {
+      0, 1, 2, 3, 4, 5, 6, 7, 9, 10, 11, 12, 13, 14, 15, 16,
+      17, 18, 19, 20, 21, 22, 23, 24, 26, 27, 28, 29, 30, 31, 32, 33,
+      34, 35, 36, 37, 38, 39, 40, 41, 42, 43, 44, 45, 46, 47, 48, 49,
+      50, 51, 52, 53, 54, 55, 56, 57, 58, 59, 60, 61, 62, 63, 64, 65,
+      66, 67, 68, 69, 70, 71, 72, 73, 74, 75, 76, 77, 78, 79, 81, 82,
+      83, 84, 85, 86, 87, 88, 89, 90, 91, 93, 94, 95, 96, 97, 98, 99,
+      100, 101, 102, 103, 105, 106, 107, 108, 109, 110, 111, 112, 113, 114, 115, 116,
+      117, 118, 119, 120, 121, 124, 125, 126, 127, 128, 129, 130, 131, 132, 133, 134,
+      135, 136, 137, 138, 139, 140, 141, 143, 144, 145, 146, 147, 148, 149, 150, 151,
+      152, 153, 154, 155, 156, 157, 158, 159, 160, 161, 163, 164, 165, 166, 167, 168,
+      169, 170, 171, 172, 173, 174, 175, 176, 177, 178, 179, 180, 181, 182, 183, 184,
+      185, 186, 187, 188, 189, 190, 191, 192, 193, 194, 195, 196, 197, 198, 199, 200,
+      201, 202, 203, 204, 205, 206, 207, 208, 209, 210, 211, 212, 213, 214, 216, 217,
+      218, 219, 220, 221, 222, 223, 224, 225, 226, 227, 228, 229, 230, 232, 233, 234,
+      236, 237, 238, 239, 240, 241, 242, 243, 244, 246, 247, 248, 249, 250, 251, 252,
+      253, 254, 255, 256, 257, 258, 259, 260, 261, 262, 263, 264, 265, 266, 267, 268,
+      269, 270, 271, 272, 273, 274, 275, 277, 278, 279, 280, 281, 282, 283, 284, 285,
+      286, 287, 289, 290, 291, 292, 293, 294, 296, 297, 298, 299, 300, 301, 302, 303,
+      304, 305, 306, 307, 308, 309, 310, 311, 312, 313, 314, 315, 316, 317, 318, 319,
+      320, 321, 323, 324, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1,
+      8, 25, 80, 92, 104, 122, 123, 142, 162, 215, 231, 235, 245, 276, 288, 295,
+      322, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1,
+      -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1,
+      -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1};
+  // LDS byte offsets within the system's area: each lane's rate operands
+  // (R x 4), and the signed rates of its species in reaction order
+  alignas(16) static constexpr uint16_t kOp[1536] = {
+      128, 384, 56, 248, 88, 184, 144, 272, 72, 128, 64, 104, 88, 384, 296, 320,
+      152, 184, 0, 240, 144, 424, 56, 112, 104, 208, 128, 248, 16, 344, 112, 128,
+      336, 416, 176, 184, 176, 408, 24, 392, 72, 360, 144, 408, 16, 200, 184, 424,
+      72, 360, 152, 264, 56, 416, 128, 408, 88, 184, 64, 232, 384, 400, 0, 264,
+      136, 144, 80, 200, 344, 424, 64, 200, 136, 272, 40, 408, 144, 152, 168, 400,
+      40, 384, 8, 120, 88, 200, 40, 264, 152, 328, 128, 248, 344, 424, 24, 288,
+      40, 296, 152, 224, 32, 72, 24, 80, 192, 384, 168, 200, 256, 368, 248, 296,
+      104, 200, 160, 416, 8, 8, 408, 424, 8, 304, 56, 200, 320, 384, 72, 312,
+      304, 336, 144, 224, 152, 264, 96, 288, 320, 344, 176, 192, 336, 424, 16, 224,
+      72, 256, 176, 352, 224, 264, 64, 288, 240, 360, 248, 416, 32, 280, 40, 264,
+      232, 296, 256, 400, 304, 424, 8, 80, 112, 320, 88, 216, 32, 168, 120, 152,
+      168, 408, 152, 392, 96, 296, 384, 400, 8, 88, 0, 320, 344, 424, 16, 168,
+      128, 192, 88, 248, 136, 320, 24, 264, 344, 408, 232, 384, 80, 376, 0, 280,
+      216, 352, 296, 416, 240, 424, 400, 416, 192, 248, 312, 344, 104, 360, 152, 392,
+      208, 368, 240, 296, 96, 328, 128, 312, 144, 232, 312, 336, 96, 368, 264, 424,
+      64, 280, 128, 128, 176, 376, 24, 248, 104, 248, 152, 256, 152, 176, 64, 184,
+      72, 136, 0, 104, 248, 424, 360, 400, 80, 312, 256, 400, 56, 128, 112, 160,
+      24, 104, 112, 400, 112, 176, 128, 320, 152, 160, 80, 136, 8, 280, 248, 424,
+      264, 416, 248, 376, 88, 312, 120, 216, 208, 224, 64, 328, 200, 208, 192, 360,
+      264, 280, 304, 312, 120, 408, 328, 424, 104, 104, 56, 280, 384, 400, 56, 200,
+      32, 80, 40, 160, 192, 288, 104, 328, 320, 384, 8, 344, 16, 368, 104, 424,
+      224, 368, 64, 296, 80, 400, 56, 64, 64, 208, 112, 344, 96, 120, 192, 400,
+      64, 232, 112, 176, 8, 88, 176, 424, 56, 336, 72, 224, 136, 272, 32, 376,
+      72, 392, 128, 384, 104, 392, 248, 368, 56, 256, 280, 296, 64, 96, 176, 424,
+      112, 112, 152, 320, 72, 96, 0, 112, 224, 408, 24, 352, 8, 40, 24, 152,
+      136, 216, 0, 416, 176, 424, 0, 320, 112, 136, 72, 376, 16, 280, 32, 200,
+      128, 304, 336, 384, 104, 416, 192, 408, 152, 392, 296, 416, 0, 0, 0, 0,
+      64, 240, 48, 256, 192, 368, 64, 392, 56, 192, 88, 384, 32, 216, 40, 376,
+      216, 288, 184, 264, 0, 0, 0, 0, 296, 416, 200, 264, 200, 280, 128, 360,
+      120, 376, 16, 328, 152, 152, 8, 128, 288, 416, 280, 360, 0, 0, 0, 0,
+      88, 96, 40, 152, 72, 208, 120, 200, 112, 416, 96, 240, 0, 128, 16, 304,
+      136, 168, 160, 312, 0, 0, 0, 0, 32, 376, 40, 408, 56, 144, 64, 296,
+      64, 72, 224, 400, 240, 296, 264, 280, 176, 384, 192, 368, 0, 0, 0, 0,
+      112, 288, 144, 200, 264, 400, 16, 288, 272, 368, 112, 152, 72, 392, 0, 256,
+      88, 216, 48, 280, 0, 0, 0, 0, 192, 264, 168, 184, 16, 344, 272, 304,
+      24, 160, 72, 400, 160, 264, 104, 296, 264, 264, 200, 288, 0, 0, 0, 0,
+      0, 344, 104, 128, 176, 408, 136, 232, 160, 360, 200, 296, 112, 144, 104, 176,
+      232, 264, 104, 240, 0, 0, 0, 0, 24, 256, 96, 344, 288, 416, 264, 312,
+      40, 416, 184, 272, 112, 216, 24, 312, 184, 416, 240, 376, 0, 0, 0, 0,
+      104, 184, 272, 352, 8, 144, 72, 200, 120, 136, 0, 344, 112, 152, 88, 408,
+      0, 176, 88, 136, 0, 0, 0, 0, 72, 280, 296, 320, 176, 296, 80, 280,
+      64, 376, 16, 280, 192, 336, 88, 344, 272, 344, 88, 240, 0, 0, 0, 0,
+      208, 264, 184, 256, 280, 416, 216, 248, 96, 208, 112, 312, 56, 216, 72, 376,
+      120, 376, 144, 216, 0, 0, 0, 0, 40, 328, 240, 336, 216, 224, 192, 400,
+      72, 392, 112, 352, 216, 336, 32, 192, 200, 400, 72, 376, 0, 0, 0, 0,
+      104, 360, 296, 416, 24, 256, 144, 216, 64, 336, 88, 224, 160, 416, 184, 368,
+      280, 344, 144, 208, 0, 0, 0, 0, 72, 312, 80, 416, 32, 216, 96, 320,
+      312, 320, 248, 272, 216, 264, 152, 312, 64, 152, 16, 144, 0, 0, 0, 0,
+      64, 104, 0, 120, 56, 144, 224, 368, 264, 328, 168, 248, 112, 240, 176, 416,
+      272, 304, 24, 168, 0, 0, 0, 0, 32, 248, 96, 344, 144, 152, 40, 352,
+      72, 312, 144, 376, 48, 128, 64, 272, 40, 192, 176, 320, 0, 0, 0, 0,
+      224, 312, 336, 360, 216, 320, 184, 272, 160, 216, 112, 368, 320, 408, 8, 232,
+      8, 32, 24, 136, 0, 0, 0, 0, 160, 184, 288, 400, 192, 224, 88, 168,
+      224, 256, 144, 168, 32, 176, 224, 272, 184, 304, 64, 392, 0, 0, 0, 0,
+      64, 280, 40, 288, 32, 392, 112, 264, 96, 160, 56, 152, 96, 344, 120, 376,
+      296, 416, 168, 408, 0, 0, 0, 0, 112, 136, 96, 104, 184, 328, 192, 248,
+      112, 248, 192, 200, 144, 312, 240, 304, 280, 368, 160, 312, 0, 0, 0, 0,
+      112, 264, 248, 400, 128, 256, 104, 328, 192, 216, 312, 320, 80, 248, 120, 384,
+      248, 336, 64, 328, 0, 0, 0, 0, 128, 160, 80, 104, 8, 160, 0, 368,
+      128, 408, 96, 264, 152, 256, 264, 280, 200, 288, 304, 360, 0, 0, 0, 0,
+      104, 264, 128, 384, 48, 360, 200, 272, 216, 288, 200, 280, 184, 200, 104, 416,
+      232, 256, 192, 248, 0, 0, 0, 0, 160, 232, 144, 152, 72, 384, 160, 200,
+      88, 384, 40, 352, 32, 184, 24, 280, 112, 296, 288, 400, 0, 0, 0, 0,
+      216, 368, 128, 408, 104, 384, 264, 368, 8, 192, 152, 184, 80, 408, 384, 400,
+      16, 176, 24, 128, 0, 0, 0, 0, 24, 328, 64, 240, 96, 304, 104, 152,
+      184, 392, 264, 312, 40, 384, 32, 264, 120, 368, 104, 144, 0, 0, 0, 0,
+      216, 392, 248, 376, 8, 72, 16, 368, 176, 296, 104, 144, 88, 264, 128, 128,
+      120, 304, 288, 336, 0, 0, 0, 0, 48, 368, 16, 128, 224, 304, 296, 336,
+      104, 264, 80, 360, 80, 312, 104, 280, 128, 240, 248, 320, 0, 0, 0, 0,
+      24, 400, 0, 48, 304, 360, 264, 264, 0, 232, 96, 128, 152, 360, 8, 248,
+      200, 344, 192, 264, 0, 0, 0, 0, 128, 288, 144, 264, 120, 184, 64, 208,
+      288, 288, 168, 352, 80, 240, 144, 184, 64, 408, 200, 400, 0, 0, 0, 0,
+      128, 304, 64, 288, 160, 272, 72, 112, 24, 56, 0, 32, 152, 280, 216, 304,
+      88, 216, 24, 192, 0, 0, 0, 0, 320, 368, 72, 184, 160, 184, 104, 104,
+      176, 376, 112, 184, 96, 344, 152, 192, 144, 360, 208, 368, 0, 0, 0, 0,
+      160, 184, 0, 168, 8, 256, 288, 376, 72, 112, 8, 336, 64, 344, 192, 224,
+      16, 40, 48, 400, 0, 0, 0, 0, 136, 264, 96, 352, 112, 200, 24, 392,
+      72, 304, 128, 160, 160, 184, 56, 280, 224, 416, 40, 392, 0, 0, 0, 0,
+      392, 400, 216, 296, 184, 264, 232, 384, 160, 304, 80, 296, 136, 288, 152, 352,
+      0, 0, 0, 0, 0, 0, 0, 0, 48, 248, 112, 232, 104, 264, 72, 392,
+      72, 88, 64, 64, 88, 168, 64, 344, 0, 0, 0, 0, 0, 0, 0, 0,
+      184, 184, 272, 392, 280, 336, 192, 224, 48, 304, 80, 272, 120, 136, 200, 224,
+      0, 0, 0, 0, 0, 0, 0, 0, 88, 184, 112, 176, 16, 168, 24, 288,
+      48, 296, 0, 176, 232, 248, 344, 416, 0, 0, 0, 0, 0, 0, 0, 0,
+      0, 416, 8, 184, 232, 296, 152, 168, 136, 176, 128, 152, 96, 200, 8, 184,
+      0, 0, 0, 0, 0, 0, 0, 0, 176, 312, 120, 416, 96, 96, 16, 376,
+      224, 408, 112, 368, 168, 360, 288, 312, 0, 0, 0, 0, 0, 0, 0, 0,
+      136, 264, 56, 360, 152, 248, 200, 280, 8, 336, 128, 400, 192, 200, 104, 240,
+      0, 0, 0, 0, 0, 0, 0, 0, 48, 360, 320, 376, 56, 328, 104, 168,
+      8, 168, 160, 416, 176, 416, 248, 272, 0, 0, 0, 0, 0, 0, 0, 0,
+      32, 360, 72, 416, 88, 352, 56, 344, 64, 352, 160, 280, 96, 112, 216, 400,
+      0, 0, 0, 0, 0, 0, 0, 0, 0, 208, 32, 392, 16, 208, 112, 184,
+      16, 344, 40, 264, 184, 192, 120, 416, 0, 0, 0, 0, 0, 0, 0, 0,
+      8, 144, 160, 216, 264, 320, 104, 232, 112, 304, 40, 352, 208, 400, 176, 200,
+      0, 0, 0, 0, 0, 0, 0, 0, 16, 152, 96, 400, 96, 344, 104, 232,
+      56, 120, 88, 296, 144, 400, 32, 304, 0, 0, 0, 0, 0, 0, 0, 0};
+  alignas(16) static constexpr uint16_t kTm[2816] = {
+      4224, 704, 816, 848, 4480, 4520, 1088, 1272, 1680, 5424, 1856, 1912, 2000, 2048, 5728, 2160,
+      2496, 2552, 2576, 2624, 6288, 3136, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 4072, 896, 4528, 4752,
+      6624, 6624, 4856, 4896, 4944, 3056, 1496, 5392, 1872, 5520, 5528, 5696, 2136, 6680, 2256, 2352,
+      2432, 6136, 2600, 6704, 6352, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 6600, 808, 4536, 4552, 4680, 1136, 4728, 1312,
+      3048, 4984, 1416, 5032, 3064, 1624, 1688, 5544, 2144, 6696, 2744, 6416, 6480, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 4232, 4376, 4400, 992, 1024, 1040, 3032, 4784, 1368, 1400, 5144, 1600,
+      5240, 5440, 1992, 2112, 2184, 2312, 2752, 2768, 2832, 2880, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      4200, 4296, 4512, 936, 4576, 4600, 1080, 1096, 4792, 4832, 5160, 1856, 5616, 5712, 2216, 5848,
+      5896, 2328, 2488, 6352, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 472, 4064, 608, 616,
+      4264, 736, 1224, 5080, 1576, 5256, 1800, 1960, 1968, 2008, 2032, 5696, 2128, 5912, 6344, 6480,
+      2904, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 592, 4392, 816, 4456, 4504, 4864, 5488, 5496,
+      5832, 2672, 2896, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 448, 488, 3008, 552, 4152, 912, 4560, 4632, 1064, 1072, 4712, 4800,
+      5016, 1440, 5200, 1760, 5440, 5560, 5792, 2392, 6200, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      4112, 560, 4176, 4288, 4320, 792, 832, 1008, 3024, 1072, 1104, 1128, 1336, 1472, 1488, 1568,
+      5168, 5224, 5272, 5296, 1896, 1896, 5536, 2064, 2248, 5968, 2408, 6192, 6712, 6328, 2776, 2800,
+      6456, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 4048, 4080, 568, 584,
+      4248, 4280, 840, 928, 4576, 1000, 4672, 4704, 1168, 4872, 4896, 1344, 1384, 5056, 5176, 5224,
+      1656, 5288, 5320, 5456, 5464, 5480, 5744, 2208, 6088, 6160, 2728, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 4120, 696, 760, 992, 4656, 1176, 3056, 5160,
+      1832, 1888, 1904, 5632, 5872, 5904, 5928, 5944, 2512, 2584, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 504, 512, 4192, 4472, 4544, 4640, 1240, 5024, 5072, 1616, 1712, 5384,
+      5480, 1976, 5568, 5592, 2192, 2200, 5920, 5992, 6136, 6704, 6256, 2704, 2712, 6464, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      4192, 648, 712, 744, 856, 952, 4672, 1208, 4888, 5000, 5000, 5048, 1632, 5280, 5344, 1784,
+      1840, 2024, 5624, 5640, 6664, 5680, 5856, 5960, 6016, 6048, 6712, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 4040, 4136, 4136, 640,
+      4240, 4272, 4288, 744, 760, 4352, 4616, 1264, 4880, 1304, 1352, 1352, 4968, 1432, 1456, 1464,
+      1472, 5136, 5144, 1824, 5416, 2088, 5688, 5704, 2168, 2176, 2304, 2344, 2448, 6112, 3112, 2576,
+      2688, 2840, 3520, 3520, 3520, 3520, 3520, 3520, 4088, 3008, 4160, 4160, 4168, 4208, 4328, 4336,
+      872, 888, 968, 1048, 1088, 1248, 1344, 4952, 1448, 1560, 1584, 5216, 1648, 1696, 1704, 1744,
+      5352, 1864, 5456, 1928, 5552, 5656, 5760, 5768, 5776, 5824, 6048, 2608, 6408, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 704, 904, 1016, 1056, 1120, 4920, 1496, 5208, 5264, 5560, 5680, 2272,
+      2288, 6688, 6000, 2472, 6304, 6424, 6432, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      4032, 456, 4096, 528, 528, 640, 4344, 768, 784, 808, 4408, 4416, 968, 976, 4632, 1112,
+      4848, 5056, 1592, 5192, 5368, 1840, 1880, 1920, 1936, 2056, 2072, 2136, 5728, 5832, 2336, 2336,
+      2520, 2832, 6440, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 4056, 4168, 4328, 4440,
+      4496, 4608, 4664, 1152, 5264, 5504, 5984, 6000, 6096, 6160, 2584, 6208, 6240, 2704, 2768, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 6592, 624, 776, 824, 4528, 960, 4568, 4712,
+      4752, 1200, 4800, 4808, 1512, 1736, 1752, 1824, 5760, 5864, 2360, 6072, 2504, 6096, 6152, 2720,
+      2736, 2744, 2840, 6472, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 464, 480, 576, 608, 776, 4536, 4568, 1016, 1032, 4808, 1304, 1408,
+      5008, 1528, 1552, 1648, 1760, 1808, 1920, 5608, 5648, 2112, 5720, 5720, 5776, 2232, 5880, 5936,
+      5952, 2376, 2400, 6080, 6104, 6168, 6216, 6328, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      4312, 4344, 4360, 4432, 944, 1048, 4856, 1288, 4928, 4936, 1576, 5240, 5248, 5328, 5344, 1880,
+      5472, 1944, 1952, 5752, 5808, 5976, 2528, 6168, 2656, 2792, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 632, 848, 984, 4600,
+      1240, 4984, 1408, 1432, 1504, 3064, 5112, 1728, 1752, 1848, 5528, 5992, 6024, 6240, 2752, 2784,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 496, 888, 4488, 4624, 4736, 4760, 1480, 5408,
+      5448, 1912, 5504, 5576, 5648, 5656, 2176, 2240, 5848, 6040, 2480, 2536, 2608, 3120, 6248, 3128,
+      6288, 2760, 6416, 6720, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 632, 3016, 4240, 672, 4312, 840, 4432, 4464, 4464, 4472, 896, 4544,
+      1232, 4840, 4920, 4936, 4960, 1448, 1480, 5072, 1672, 1808, 5400, 1864, 2064, 2224, 5888, 5896,
+      2360, 5976, 2432, 6056, 6080, 2640, 6280, 6360, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      4096, 4104, 4216, 4688, 1192, 4824, 1256, 1392, 5088, 5200, 1768, 5360, 5392, 2080, 5672, 2096,
+      2120, 5784, 2216, 2376, 2384, 6032, 6056, 2536, 2664, 6344, 2816, 2864, 2880, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 488, 600, 624, 6600,
+      1064, 3024, 1096, 4696, 1120, 1168, 1280, 1288, 4952, 1424, 1504, 1664, 1768, 1792, 5592, 5664,
+      5888, 2416, 6016, 6032, 2480, 2512, 6112, 2680, 6312, 6392, 6448, 2872, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 4040, 4256, 4520, 4704, 1336, 5032, 5128, 5152,
+      5168, 5280, 5664, 6064, 2736, 2888, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 504, 4368, 4384, 864, 944, 1056, 1184, 4776, 1200, 4792, 4816, 5328,
+      5360, 5376, 5712, 5768, 5792, 5800, 5816, 2368, 2464, 6144, 6208, 6224, 6256, 2720, 6464, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      480, 4144, 568, 4304, 4592, 4776, 1216, 4824, 4904, 3048, 1392, 1512, 5152, 5184, 1640, 1712,
+      5336, 5512, 2264, 2384, 2416, 6488, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 4360, 872, 1152, 1376,
+      4992, 1456, 1464, 1488, 1536, 5424, 2256, 6008, 6128, 6152, 6192, 6272, 6400, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 4176, 680, 792, 5104, 1544, 1632, 6656, 5736,
+      5824, 2280, 5944, 2448, 2496, 2688, 2696, 2712, 6440, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 448, 456, 512, 4104, 544, 4296, 752, 800, 4456, 1040, 1184, 1256,
+      5008, 1520, 5136, 1720, 1728, 5352, 2016, 2104, 6672, 3096, 5872, 2352, 6008, 2456, 2520, 6384,
+      2816, 2856, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      4080, 536, 592, 4232, 672, 4784, 4848, 4944, 1552, 5336, 5600, 2160, 5880, 2544, 6200, 6400,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 464, 4128, 600, 4216,
+      4256, 4336, 4352, 824, 4440, 4496, 4592, 1024, 4720, 1160, 1248, 1296, 1328, 1328, 4960, 4968,
+      5040, 5312, 1784, 1816, 5416, 1960, 2000, 2008, 5608, 2032, 3080, 2152, 5752, 5816, 2296, 2328,
+      5920, 6176, 2640, 6264, 6264, 6272, 2864, 3520, 4056, 656, 880, 960, 4664, 1144, 1232, 1280,
+      4928, 5232, 1672, 1720, 1904, 2248, 2264, 2456, 6296, 6336, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 4112, 552, 4248, 4320, 4680, 4696, 1176, 4768, 4976, 1424, 1688, 1792,
+      1952, 5616, 2048, 2152, 6680, 2296, 2312, 2344, 5952, 2392, 6176, 2616, 2648, 2672, 6320, 6376,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      4208, 728, 736, 4408, 832, 1008, 1136, 3032, 4744, 1360, 1400, 5376, 5432, 5432, 2024, 5672,
+      5984, 2440, 6224, 6232, 2680, 6392, 2824, 2848, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 4064, 560, 4184, 664,
+      688, 864, 1128, 4760, 1320, 4992, 1544, 1664, 5408, 1888, 5496, 1976, 1984, 2016, 5624, 5736,
+      2168, 6128, 2560, 2616, 2632, 6368, 6408, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 4072, 4416, 1144, 4888, 4904, 4912, 6640, 5096,
+      5192, 5464, 5472, 5488, 5552, 2144, 2280, 2368, 2488, 2592, 6336, 6360, 2808, 6432, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 520, 4120, 4280, 4304, 4488, 1000, 4640, 1160, 1696, 5304, 5320, 1776,
+      1816, 2056, 2184, 2232, 5864, 5928, 2440, 2568, 2592, 2656, 2792, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      4088, 576, 664, 4424, 920, 4584, 4608, 1208, 4816, 5040, 5304, 1776, 1984, 2072, 5840, 6120,
+      2552, 6184, 2760, 2856, 3136, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 4264, 4376, 4840, 1264,
+      5016, 1568, 1624, 5312, 5640, 2088, 3104, 6104, 2800, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 4152, 680, 720, 1320, 6632, 4976, 5064, 5096,
+      1608, 5296, 1872, 5520, 5784, 5800, 2568, 6384, 2848, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 520, 4224, 648, 712, 4552, 6608, 4728, 6616, 1440, 5048, 6648, 5120,
+      1584, 1680, 5544, 2200, 5856, 5960, 5968, 2408, 2424, 6120, 2600, 6296, 6320, 6448, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      496, 656, 856, 1224, 5024, 1600, 1704, 1800, 1848, 5536, 1968, 2400, 6144, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 4048, 4272, 720, 912,
+      4504, 4512, 4616, 1112, 4864, 4912, 5104, 5248, 1832, 2080, 3088, 5936, 6024, 6088, 2648, 2808,
+      6472, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 4144, 4368, 4392, 4424, 4688, 1216, 1272, 1296,
+      1312, 5128, 5232, 1744, 1928, 5600, 6664, 2104, 2224, 6696, 2664, 6376, 6424, 2888, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 544, 584, 4200, 800, 920, 4624, 1080, 1360, 1416, 5208, 5272, 1736,
+      5448, 5632, 2128, 2208, 2272, 2696, 6304, 2728, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      4032, 768, 4584, 4648, 4872, 4880, 1376, 5080, 5088, 1536, 1592, 1608, 1616, 5384, 5568, 5584,
+      2040, 2288, 2320, 5912, 6184, 6248, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 4384, 4448, 880, 936,
+      1032, 1104, 4832, 1368, 1384, 1528, 5176, 5288, 5400, 1992, 5688, 5744, 6216, 2776, 2904, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 536, 728, 752, 4400, 4448, 952, 984, 4648,
+      4656, 4720, 1192, 1560, 1640, 1656, 3072, 1936, 5584, 2040, 2096, 3088, 2320, 2464, 6064, 6072,
+      2544, 6312, 2824, 2872, 2896, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 472, 616, 784, 976, 4736, 3040, 5112, 5120, 5184, 5368, 5512, 5576,
+      2120, 2192, 5840, 6688, 5904, 2504, 2784, 6456, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      4128, 4184, 688, 696, 4480, 904, 928, 4560, 4744, 4768, 5064, 1520, 5216, 5256, 3072, 1944,
+      5704, 5808, 2240, 2304, 2424, 6040, 2472, 2528, 2560, 2624, 2632, 6232, 6280, 6368, 6488, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520,
+      3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520, 3520};
+  struct Lane {
+    double kf[R], kr[R];
+    double W[S], iW[S];
+    double rho, irho;
+    uint32_t op[R][4], tm[kTermLen];   // LDS addresses, formed once per system
+    uint32_t c_at;
+  };
+  __device__ __attribute__((noinline)) static void rates(Params p, double T, double* lds, int r) {
+    const double lnT = crm::cr_log(T);
+    double* const Q = lds + kOffQ;
+#pragma nounroll
+    for (int m = 0; m < R; ++m) {
+      const int j = kRxOf[m * kL + r];
+      Q[m * kL + r] = j >= 0 ? crm::cr_exp(p[j] + p[NR + j] * lnT - p[2 * NR + j] / T) : 0.0;
+    }
+  }
+  __device__ static void init(Lane& L, const Params& p, const double* __restrict__ g, int64_t i,
+                              int64_t n, const Grp<WNet>& x) {
+    double* const Q = x.lds + kOffQ;
+    rates(p, g[i], x.lds, x.r);
+#pragma unroll
+    for (int m = 0; m < R; ++m) {
+      const int j = kRxOf[m * kL + x.r];
+      L.kf[m] = Q[m * kL + x.r];
+      L.kr[m] = j >= 0 ? L.kf[m] * p[3 * NR + j] : 0.0;
+    }
+    const int k = x.sp[0];
+    L.W[0] = k >= 0 ? p[4 * NR + k] : 0.0;
+    L.iW[0] = k >= 0 ? p[4 * NR + N + k] : 0.0;
+    L.rho = g[n + i];
+    L.irho = 1.0 / L.rho;
+    const uint32_t base = lds_address(x.lds);
+    L.c_at = base + 8 * (k >= 0 ? k : N + 1);
+#pragma unroll
+    for (int q = 0; q < 4 * R; ++q) L.op[q / 4][q % 4] = base + kOp[x.r * 4 * R + q];
+#pragma unroll
+    for (int t = 0; t < kTermLen; ++t) L.tm[t] = base + kTm[x.r * kTermLen + t];
+    if (x.r == 0) x.lds[kOffZero] = 0.0;
+  }
+};
+
 }  // namespace gen_n53r325_7a51609a
 
 template <>

@@ -53,6 +53,16 @@ struct Grp {
   int sp[GP::S];
 };
 
+// A group problem with one species per lane (GP::kWide, group_rhs_wide).
+template <class GP, class = void>
+struct GroupWide {
+  static constexpr bool value = false;
+};
+template <class GP>
+struct GroupWide<GP, std::void_t<decltype(GP::kWide)>> {
+  static constexpr bool value = GP::kWide;
+};
+
 // Orders the group's LDS accesses (one wave per workgroup: no barrier wait).
 __device__ inline void group_sync() { __syncthreads(); }
 
@@ -62,6 +72,14 @@ __device__ inline void group_sync() { __syncthreads(); }
 __device__ inline void opaque(uint32_t& v) { asm volatile("" : "+v"(v)); }
 // The same for a double: the value is formed here, not later.
 __device__ inline void opaque_f64(double& v) { asm volatile("" : "+v"(v)); }
+
+// The address of an LDS object, and the double at one.
+__device__ inline uint32_t lds_address(const double* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) double*)p;
+}
+__device__ inline __attribute__((address_space(3))) double* lds_at(uint32_t a) {
+  return (__attribute__((address_space(3))) double*)(uintptr_t)a;
+}
 
 template <class GP>
 __device__ inline bool owns(const Grp<GP>& x, int m) {
@@ -171,9 +189,59 @@ __device__ void group_chain_sum2(const Grp<GP>& x, const double* u, const double
 
 // sum_k t_k over k = 0..N-1 in order, t_k held by the owners; every lane of
 // the group gets the same value.
+//
+// The wide variants read all values in every lane instead of passing the sum
+// along the chain of lanes (the same additions; the reads are broadcasts), six
+// pairs ahead of the additions.
+template <class GP>
+struct LaneSum {
+  static constexpr int kPairs = (GP::N + 1) / 2, kAhead = 6;
+  static constexpr int kChunks = (kPairs + kAhead - 1) / kAhead;
+  const double2* p;
+  double2 next[kAhead];
+  double s;
+  __device__ LaneSum(const double* v) : p(reinterpret_cast<const double2*>(v)), s(0.0) { read(0); }
+  __device__ void read(int c) {
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q)
+      if (c * kAhead + q < kPairs) next[q] = p[c * kAhead + q];
+  }
+  // Chunk c's additions, the next chunk's reads issued before them.
+  __device__ void step(int c) {
+    double2 now[kAhead];
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) now[q] = next[q];
+    if (c + 1 < kChunks) read(c + 1);
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) {
+      const int k = 2 * (c * kAhead + q);
+      if (k < GP::N) s += now[q].x;
+      if (k + 1 < GP::N) s += now[q].y;
+    }
+  }
+};
+
+template <class GP>
+__device__ double lane_sum(const double* v) {
+  LaneSum<GP> sum(v);
+#pragma unroll
+  for (int c = 0; c < LaneSum<GP>::kChunks; ++c) {
+    sum.step(c);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  return sum.s;
+}
+
 template <class GP>
 __device__ double group_sum(const Grp<GP>& x, const double (&t)[GP::S]) {
   double* red = x.lds + GP::kOffRed;
+  if constexpr (GroupWide<GP>::value) {
+    if (owns<GP>(x, 0)) red[x.sp[0]] = t[0];
+    group_sync();
+    const double s = lane_sum<GP>(red);
+    group_sync();
+    return s;
+  } else {
 #pragma unroll
   for (int m = 0; m < GP::S; ++m)
     if (owns<GP>(x, m)) red[x.sp[m]] = t[m];
@@ -181,6 +249,7 @@ __device__ double group_sum(const Grp<GP>& x, const double (&t)[GP::S]) {
   const double s = group_chain_sum<GP, GP::N>(x, red);
   group_sync();
   return s;
+  }
 }
 
 // max(0, max_k t_k) with fmax, t_k >= +0 or NaN: the largest non-NaN value (or
@@ -239,6 +308,9 @@ template <class GP>
 __device__ void group_rhs_mass_action(const typename GP::Lane& L, const Grp<GP>& x,
                                       const double (&y)[GP::S], double (&f)[GP::S]);
 template <class GP>
+__device__ void group_rhs_wide(const typename GP::Lane& L, const Grp<GP>& x,
+                               const double (&y)[GP::S], double (&f)[GP::S]);
+template <class GP>
 __device__ void group_rhs_thermal(const typename GP::Lane& L, const Grp<GP>& x,
                                   const double (&y)[GP::S], double (&f)[GP::S]);
 
@@ -250,6 +322,8 @@ __device__ void group_rhs(const typename GP::Lane& L, const Grp<GP>& x, const do
     GP::rhs(L, x, y, f);
   else if constexpr (GroupThermal<GP>::value)
     group_rhs_thermal<GP>(L, x, y, f);
+  else if constexpr (GroupWide<GP>::value)
+    group_rhs_wide<GP>(L, x, y, f);
   else
     group_rhs_mass_action<GP>(L, x, y, f);
 }
@@ -352,6 +426,90 @@ __device__ void group_rhs_mass_action(const typename GP::Lane& L, const Grp<GP>&
   }
   f[0] = owns<GP>(x, 0) ? (L.W[0] * om0) * L.irho : 0.0;
   f[1] = owns<GP>(x, 1) ? (L.W[1] * acc) * L.irho : 0.0;
+}
+
+// Mass action with one species per lane (64 lanes per system at 53 species, 32
+// at 32): the same exchange, with every LDS address kept in a register (no code
+// tables to read and decode), one sum of terms per lane and [M] added up by
+// every lane.  What bounds it is the latency of one evaluation: two chains of
+// dependent additions (N for [M], the longest species' terms) and four LDS
+// round trips, about 2100 cycles at 53 species against 5000 for the group
+// variant's two species per lane, whose instructions also serve two systems.
+// So it runs the batches whose slowest systems decide (times in ms, group
+// variant -> wide; RKCK spreads its step counts over a factor of twenty):
+//   53 species RKCK  200 systems 117 -> 46, 2048 207 -> 92, 16411 362 -> 272,
+//                    32768 552 -> 521, 65536 855 -> 930
+//   53 species RKC   200 systems 49 -> 27, 1024 59 -> 34, 2048 59 -> 57,
+//                    4096 68 -> 95
+//   32 species RKCK  200 systems 290 -> 110, 16411 395 -> 241, 65536 768 -> 679
+//   32 species RKC   200 systems 65 -> 33, 4096 83 -> 47, 16411 144 -> 131
+// RKC at 53 species is compiled for one wave per SIMD (at two it spills 133
+// registers: 27 -> 37 ms at 200 systems).
+template <class GP>
+__device__ void group_rhs_wide(const typename GP::Lane& L, const Grp<GP>& x,
+                               const double (&y)[GP::S], double (&f)[GP::S]) {
+  static_assert(GP::S == 1 && GP::kOffC == 0 && GP::kNegOff % 64 == 0, "one species per lane");
+  static_assert(GP::kMSlot > 0, "[M] formed before its slots");
+  static_assert(GP::N + 1 < GP::kOffQ && GP::kOffZero == GP::kOffQ + GP::R * GP::kL &&
+                    GP::kOffZero < GP::kOffRed &&
+                    GP::kOffRed + GP::N <= GP::kOffQ + GP::kNegOff &&
+                    GP::kOffQ + GP::kNegOff + GP::R * GP::kL <= GP::kLdsPerSystem,
+                "C, +q, the zero, the scratch and -q are disjoint");
+  double* const Q = x.lds + GP::kOffQ + x.r;
+  *lds_at(L.c_at) = (L.rho * y[0]) * L.iW[0];
+  group_sync();
+  // one slot after the other, each with the next slot's operands read ahead and
+  // a part of [M]'s additions beside it: a wave of a small batch has its SIMD to
+  // itself, so every LDS latency and every dependent addition shows
+  constexpr int kR = GP::R, kSteps = GP::kMSlot < 1 ? 1 : GP::kMSlot;
+  const uint32_t m_at = lds_address(x.lds) + 8 * GP::N;
+  double a[2][4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) a[0][q] = *lds_at(L.op[0][q]);
+  LaneSum<GP> sum(x.lds);
+  constexpr int kChunks = LaneSum<GP>::kChunks;
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int m = 0; m < kR; ++m) {
+    double (&c)[4] = a[m % 2];
+    if (m + 1 < kR)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a[(m + 1) % 2][q] = *lds_at(L.op[m + 1][q]);
+#pragma unroll
+    for (int k = 0; k < kChunks; ++k)
+      if (k * kSteps / kChunks == m) sum.step(k);
+    if (m >= GP::kMSlot) {
+      c[1] = L.op[m][1] == m_at ? sum.s : c[1];
+      c[3] = L.op[m][3] == m_at ? sum.s : c[3];
+    }
+    const double q = (L.kf[m] * c[0]) * c[1] - (L.kr[m] * c[2]) * c[3];
+    Q[m * GP::kL] = q;
+    Q[m * GP::kL + GP::kNegOff] = -q;
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  group_sync();
+  // the terms, one batch read ahead of the additions
+  constexpr int kB = 12, kT = GP::kTermLen, kBatches = (kT + kB - 1) / kB;
+  double acc = 0.0, next[kB];
+#pragma unroll
+  for (int t = 0; t < kB; ++t)
+    if (t < kT) next[t] = *lds_at(L.tm[t]);
+#pragma unroll
+  for (int b = 0; b < kBatches; ++b) {
+    double now[kB];
+#pragma unroll
+    for (int t = 0; t < kB; ++t) now[t] = next[t];
+#pragma unroll
+    for (int t = 0; t < kB; ++t)
+      if ((b + 1) * kB + t < kT) next[t] = *lds_at(L.tm[(b + 1) * kB + t]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < kB; ++t)
+      if (b * kB + t < kT) acc = acc + now[t];
+    opaque_f64(acc);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  f[0] = owns<GP>(x, 0) ? (L.W[0] * acc) * L.irho : 0.0;
 }
 
 // Mass action with the energy equation (Sec. 4.2 at constant volume): the
@@ -1246,6 +1404,27 @@ int launch_with_group(const LaunchArgs* a, void* stream) {
                                     : launch_group_method<GP, kMethodRkc, true>(a, s);
   return a->method == kMethodRkck ? launch_group_method<GP, kMethodRkck, false>(a, s)
                                   : launch_group_method<GP, kMethodRkc, false>(a, s);
+}
+
+// Launches the wide variant WP for batches of up to its kMaxRkc / kMaxRkck
+// systems per SIMD, the group kernels of GP for larger ones, and the one-lane
+// kernels as launch_with_group does.
+template <class Prob, class GP, class WP>
+int launch_with_wide(const LaunchArgs* a, void* stream) {
+  const hipStream_t s = static_cast<hipStream_t>(stream);
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return kLaunchHip;
+  const int64_t most = (a->method == kMethodRkck ? WP::kMaxRkck : WP::kMaxRkc) * (int64_t)cus * 4;
+  if (a->schedule == kSchedPlain || a->schedule == kSchedPersistent || !a->ws ||
+      a->ws_bytes < kQueueBytes || a->n > most)
+    return launch_with_group<Prob, GP>(a, stream);
+  if (a->pilot)
+    return a->method == kMethodRkck ? launch_group_method<WP, kMethodRkck, true>(a, s)
+                                    : launch_group_method<WP, kMethodRkc, true>(a, s);
+  return a->method == kMethodRkck ? launch_group_method<WP, kMethodRkck, false>(a, s)
+                                  : launch_group_method<WP, kMethodRkc, false>(a, s);
 }
 
 // Launches the group kernels of GP under every schedule (problems without
