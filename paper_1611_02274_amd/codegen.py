@@ -849,7 +849,7 @@ struct WNet {{
   static constexpr bool kWide = true;
   // largest batches it runs, in systems per SIMD (rk_group.hpp group_rhs_wide)
   static constexpr int kMaxRkck = {64 if n <= 32 else 32};
-  static constexpr int kMaxRkc = {16 if n <= 32 else 2};
+  static constexpr int kMaxRkc = {24 if n <= 32 else 2};
   static constexpr int N = {n};
   static constexpr int NR = {G["nr"]};
   static constexpr int kL = {G["L"]};

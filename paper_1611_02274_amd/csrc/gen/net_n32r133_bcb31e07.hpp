@@ -1095,7 +1095,7 @@ struct WNet {
   static constexpr bool kWide = true;
   // largest batches it runs, in systems per SIMD (rk_group.hpp group_rhs_wide)
   static constexpr int kMaxRkck = 64;
-  static constexpr int kMaxRkc = 16;
+  static constexpr int kMaxRkc = 24;
   static constexpr int N = 32;
   static constexpr int NR = 133;
   static constexpr int kL = 32;

@@ -540,6 +540,10 @@ int launch_adjoint(const AdjointArgs* a, void* stream) {
   int lanes;
   bool sparse;
   if (spread_lanes<Prob>(a->n, &lanes, &sparse) != kLaunchOk) return kLaunchHip;
+  // whole 128-byte lines of the workspace columns per wave: the sweep is bound by
+  // that traffic (9 species RKCK 16646 systems, forward and back: 77.7 ms with 17
+  // systems per wave, 62.9 with 32; 13 species 13.8 and 11.9)
+  lanes = (lanes + 15) / 16 * 16;
   const dim3 waves((unsigned)((a->n + lanes - 1) / lanes));
   const auto run = [&](auto kernel) {
     kernel<<<waves, dim3(kLdsStride), 0, s>>>(a->prm, a->n, a->g, T, ck ? 0 : a->max_stages, a->w,
