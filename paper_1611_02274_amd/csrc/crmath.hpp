@@ -201,8 +201,29 @@ RKMI_HD dd log_dd(double x) {
 // R.hi, the exact value rounds to R.hi; that fails for about 2^-17 of inputs
 // (and where R.hi is a power of two), which take exp_dd, as do the ends of the
 // range (subnormal results, overflow, NaN).
-RKMI_HD double cr_exp(double x) {
-  if (!(x > -708.3 && x < 709.7)) return exp_dd(x, 0.0);
+//
+// The tables of the reduction are read through Tab (dd t1(j), dd t2(j)): the
+// constants themselves, or a copy a kernel keeps in LDS, whose reads take a
+// fraction of the constants' latency.
+struct ExpConstants {
+  RKMI_HD dd t1(int j) const { return {kExpT1[2 * j], kExpT1[2 * j + 1]}; }
+  RKMI_HD dd t2(int j) const { return {kExpT2[2 * j], kExpT2[2 * j + 1]}; }
+};
+constexpr int kExpTableDoubles = 128;
+struct ExpTable {
+  const double* p;   // kExpTableDoubles, 16-byte aligned: the t1 pairs, the t2 pairs
+  RKMI_HD dd t1(int j) const { return {p[2 * j], p[2 * j + 1]}; }
+  RKMI_HD dd t2(int j) const { return {p[64 + 2 * j], p[64 + 2 * j + 1]}; }
+};
+// Entry k of an ExpTable.
+RKMI_HD double exp_table_entry(int k) { return k < 64 ? kExpT1[k] : kExpT2[k - 64]; }
+
+// The first evaluation, without a branch; *ok: its value is exp(x) as cr_exp
+// rounds it, else exp_dd decides.
+template <class Tab>
+RKMI_HD double exp_try(double arg, const Tab& tab, bool& ok) {
+  const bool in = arg > -708.3 && arg < 709.7;
+  const double x = in ? arg : 0.0;
   const double kd = rint(x * kInvL);
   const double rh = x - kd * kL1;                  // exact
   const dd p = two_prod(kd, kL2);
@@ -213,15 +234,37 @@ RKMI_HD double cr_exp(double x) {
                                          r * (0x1.5555555555555p-5 + r * 0x1.1111111111111p-7)));
   const dd e1 = fast_two_sum(1.0, r);
   const dd E = fast_two_sum(e1.hi, e1.lo + ((rl + rl * r) + q));
-  const int64_t k = (int64_t)kd;
-  const int64_t m = k >> 10;
-  const int jj = (int)(k - (m << 10));
-  const int j1 = jj >> 5, j2 = jj & 31;
-  const dd T = dd_mul(dd{kExpT1[2 * j1], kExpT1[2 * j1 + 1]}, dd{kExpT2[2 * j2], kExpT2[2 * j2 + 1]});
+  const int k = (int)kd;                           // |k| < 2^21
+  const dd T = dd_mul(tab.t1((k >> 5) & 31), tab.t2(k & 31));
   const dd R = dd_mul(T, E);
   const double half_ulp = R.hi >= 2.0 ? 0x1p-52 : (R.hi >= 1.0 ? 0x1p-53 : 0x1p-54);
-  if (fabs(R.lo) < half_ulp - 0x1p-70 && R.hi != 1.0 && R.hi != 2.0) return scale2(R.hi, (int)m);
-  return exp_dd(x, 0.0);
+  ok = in && fabs(R.lo) < half_ulp - 0x1p-70 && R.hi != 1.0 && R.hi != 2.0;
+  // times 2^(k >> 10): the result is normal for these arguments
+  return from_bits(bits_of(R.hi) + ((uint64_t)(uint32_t)(k >> 10) << 52));
+}
+
+RKMI_HD double cr_exp(double x) {
+  bool ok;
+  const double y = exp_try(x, ExpConstants{}, ok);
+  return ok ? y : exp_dd(x, 0.0);
+}
+
+// y[k] = cr_exp(x[k]): the first evaluations side by side (independent
+// operations between each other's dependent ones), then whatever exp_dd has to
+// decide.
+template <int K, class Tab>
+RKMI_HD void cr_exp_n(const double (&x)[K], double (&y)[K], const Tab& tab) {
+  bool ok[K], all = true;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    y[k] = exp_try(x[k], tab, ok[k]);
+    all = all && ok[k];
+  }
+  if (!all) {
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if (!ok[k]) y[k] = exp_dd(x[k], 0.0);
+  }
 }
 
 RKMI_HD double cr_log(double x) {

@@ -101,6 +101,28 @@ struct WavesPerEu<P, std::void_t<decltype(P::kWavesPerEu)>> {
   static constexpr int value = P::kWavesPerEu;
 };
 
+// Doubles a workgroup's lanes share in LDS, before the lanes' slots: an ExpTable
+// for the problems that form exponentials in every evaluation
+// (Prob::kExpTable), else none.
+template <class P, class = void>
+struct SharedDoubles {
+  static constexpr int value = 0;
+};
+template <class P>
+struct SharedDoubles<P, std::void_t<decltype(P::kExpTable)>> {
+  static constexpr int value = P::kExpTable ? crm::kExpTableDoubles : 0;
+};
+
+// The shared doubles in front of a lane's slot.
+template <class P>
+RKMI_HD double* shared_area(double* slot) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return slot - threadIdx.x - SharedDoubles<P>::value;
+#else
+  return slot - SharedDoubles<P>::value;
+#endif
+}
+
 // The variant of a problem that runs batches of at most one wave per SIMD: the
 // problem itself, or the one generated for them.
 template <class P>
@@ -967,10 +989,16 @@ RKMI_HD void integrate_system(const typename Prob::Params& prm, int64_t n, int64
 // columns per workgroup).
 template <class Prob, int Method>
 __device__ double* lane_slot(double* lds, double* cols) {
-  if constexpr (Prob::kColumns)
+  if constexpr (Prob::kColumns) {
     return cols + (int64_t)blockIdx.x * (slot_doubles<Prob, Method>() * kLdsStride) + threadIdx.x;
-  else
+  } else if constexpr (SharedDoubles<Prob>::value > 0) {
+    for (int k = threadIdx.x; k < crm::kExpTableDoubles; k += kLdsStride)
+      lds[k] = crm::exp_table_entry(k);
+    __syncthreads();
+    return lds + SharedDoubles<Prob>::value + threadIdx.x;
+  } else {
     return lds + threadIdx.x;
+  }
 }
 
 template <class Prob, int Method>
@@ -1004,7 +1032,8 @@ __attribute__((amdgpu_waves_per_eu(WavesPerEu<Prob>::value))) void plain_kernel(
                                                            const int32_t* __restrict__ order,
                                                            double* __restrict__ carry,
                                                            int lanes) {
-  __shared__ double lds[kernel_lds_doubles<Prob, Method>() * kLdsStride];
+  __shared__ __attribute__((aligned(16)))
+  double lds[kernel_lds_doubles<Prob, Method>() * kLdsStride + SharedDoubles<Prob>::value];
   const int64_t q = spread_position(n, lanes);
   const int64_t i = order ? (int64_t)order[q] : q;
   integrate_system<Prob, Method>(prm, n, i, y0, y1, g, c, status, stats,
@@ -1023,7 +1052,7 @@ __attribute__((amdgpu_waves_per_eu(WavesPerEu<Prob>::value))) void plain_kernel(
 // wave leaves it.  Queue position q is system order[q] (q without a map).
 // Called by all 64 lanes of the wave.
 template <class Prob, int Method>
-__device__ void persistent_loop(const typename Prob::Params& prm, int64_t n, const double* y0,
+__device__ __forceinline__ void persistent_loop(const typename Prob::Params& prm, int64_t n, const double* y0,
                                 double* y1, const double* g, const Ctl& c, int32_t* status,
                                 int32_t* stats, unsigned long long* queue, double* slot,
                                 const int32_t* order, double* carry) {
@@ -1078,7 +1107,8 @@ __attribute__((amdgpu_waves_per_eu(WavesPerEu<Prob>::value))) void persistent_ke
                                                                 double* cols,
                                                                 const int32_t* __restrict__ order,
                                                                 double* __restrict__ carry) {
-  __shared__ double lds[kernel_lds_doubles<Prob, Method>() * kLdsStride];
+  __shared__ __attribute__((aligned(16)))
+  double lds[kernel_lds_doubles<Prob, Method>() * kLdsStride + SharedDoubles<Prob>::value];
   persistent_loop<Prob, Method>(prm, n, y0, y1, g, c, status, stats, queue,
                                 lane_slot<Prob, Method>(lds, cols), order, carry);
 }

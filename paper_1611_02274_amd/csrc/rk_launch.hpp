@@ -170,22 +170,24 @@ int host_run(const LaunchArgs* a) {
                                         ? slot_doubles<Prob, kMethodRkck>()
                                         : slot_doubles<Prob, kMethodRkc>()) *
                                kLdsStride +
-                           1);
+                           1 + SharedDoubles<Prob>::value);
+  for (int k = 0; k < SharedDoubles<Prob>::value; ++k) slot[k] = crm::exp_table_entry(k);
+  double* const lane = slot.data() + SharedDoubles<Prob>::value;
   for (int64_t i = 0; i < a->n; ++i) {
     if constexpr (HasGershgorin<Prob>::value && !SigmaFromGershgorin<Prob>::value) {
       if (a->method == kMethodRkc && a->ctl.sr_method == kSrGershgorin) {
         integrate_system<WithGershgorin<Prob>, kMethodRkc>(a->prm, a->n, i, a->y0, a->y1, a->g,
                                                            a->ctl, a->status, a->stats,
-                                                           slot.data(), a->carry);
+                                                           lane, a->carry);
         continue;
       }
     }
     if (a->method == kMethodRkck)
       integrate_system<Prob, kMethodRkck>(a->prm, a->n, i, a->y0, a->y1, a->g, a->ctl, a->status,
-                                          a->stats, slot.data(), a->carry);
+                                          a->stats, lane, a->carry);
     else
       integrate_system<Prob, kMethodRkc>(a->prm, a->n, i, a->y0, a->y1, a->g, a->ctl, a->status,
-                                         a->stats, slot.data(), a->carry);
+                                         a->stats, lane, a->carry);
   }
   return 0;
 }
