@@ -456,14 +456,17 @@ extern "C" int64_t rkmi_gen_{tag}_workspace(int method, int schedule, int64_t n)
 
 
 def thermal_group_source(net, tag: str) -> tuple[str, str]:
-    """The network with the energy equation on the group schedule (32 lanes
-    per system, rk_group.hpp group_rhs_thermal): unknowns (T, Y_1..Y_N) over the
-    lanes' slots, the rate coefficients k_f,j(T) formed by each position's lane
-    at every evaluation, the species part as the isothermal group right-hand
-    side, and dT/dt from two species sums passed along the chain of lanes.
-    Same operations in the same order as the reference evaluation."""
+    """The network with the energy equation on the group schedule (32 lanes per
+    system, rk_group.hpp group_rhs_thermal) and, for small batches, one unknown
+    per lane of a wave (group_rhs_thermal_wide): unknowns (T, Y_1..Y_N), the
+    rate coefficients k_f,j(T) formed by each position's lane at every
+    evaluation, and dT/dt from two species sums.  Same operations in the same
+    order as the reference evaluation."""
     n, nr = net.n_sp, net.n_rx
     G = _group_layout(net, 32, thermal=True)
+    W = _wide_layout(net, 64, thermal=True)
+    kg, kw = (min((3, 4, 5), key=lambda k: (-X["R"] % k, k)) for X in (G, W))
+    prm = 4 * nr + 5 * n + (4 * nr + 5 * n) % 2
     header = f"""// Generated by paper_1611_02274_amd/codegen.py -- do not edit.
 // Mass-action network with the energy equation on the group schedule: {n} species
 // + T, {nr} reversible reactions (topology {tag}).
@@ -477,6 +480,7 @@ namespace gen_{tag} {{
 
 struct GNet {{
   static constexpr bool kThermal = true;
+  static constexpr bool kExpTable = true;
   static constexpr int NS = {n};
   static constexpr int N = NS + 1;    // unknowns: T, then the species
   static constexpr int NR = {nr};
@@ -488,6 +492,7 @@ struct GNet {{
   static constexpr int kWavesPerEuRkck = 2;
   static constexpr int S = {G["S"]};
   static constexpr int R = {G["R"]};
+  static constexpr int kExps = {kg};    // exponentials formed side by side
   static constexpr int kMSlot = {G["m_first"]};   // first slot that may hold a [M] reaction
   static constexpr int kOffC = 0;
   static constexpr int kOffT = NS + 1;            // T, written by its owner
@@ -503,11 +508,14 @@ struct GNet {{
   static constexpr int kTermWords = {G["n_words"]};
   static constexpr int kTermLen = {G["tot"]};
   static constexpr int kChunk = {G["chunk"]};
-  // uniform data: [lnA | beta | Ea | 1/K | W | 1/W | u0 | cv0 | cv1]
+  // uniform data: [lnA | beta | Ea | 1/K | W | 1/W | u0 | cv0 | cv1], then (lnA,
+  // beta, Ea, 1/K) of each position's reaction, here and in the wide variant
+  static constexpr int kPrmOffset = {prm};
   using Params = const double*;
 {_group_tables(G)}
   struct Lane {{
     const double* prm;   // the uniform data (rate parameters read at every evaluation)
+    crm::ExpTable et;
     double W[S], iW[S], u0[S], cv0[S], cv1[S];
     double rho, irho;
     int bnd;   // chunks of the slot-0 list
@@ -515,6 +523,7 @@ struct GNet {{
   __device__ static void init(Lane& L, const Params& p, const double* __restrict__ g, int64_t i,
                               int64_t, const Grp<GNet>& x) {{
     L.prm = p;
+    L.et = shared_exp_table(x);
 #pragma unroll
     for (int m = 0; m < S; ++m) {{
       const int k = x.sp[m] - 1;   // species of the slot (T and empty slots: none)
@@ -533,6 +542,75 @@ struct GNet {{
   }}
 }};
 
+// Wide variant: one unknown per lane of a wave (rk_group.hpp).
+struct WNet {{
+  static constexpr bool kThermal = true;
+  static constexpr bool kWide = true;
+  // largest batches it runs, in systems per SIMD (rk_group.hpp group_rhs_thermal_wide)
+  static constexpr int kMaxRkck = {8 if n <= 32 else 16};
+  static constexpr int kMaxRkc = {1 if n <= 32 else 2};
+  static constexpr bool kExpTable = true;
+  static constexpr int NS = {n};
+  static constexpr int N = NS + 1;    // unknowns: T, then the species
+  static constexpr int NR = {nr};
+  static constexpr int kL = 64;
+  static constexpr int kGroupLanes = 64;
+  static constexpr bool kColumns = false;
+  static constexpr int kLaneDoubles = 0;
+  static constexpr int kWavesPerEuRkc = 1;
+  static constexpr int kWavesPerEuRkck = 1;
+  static constexpr int S = 1;
+  static constexpr int R = {W["R"]};
+  static constexpr int kExps = {kw};    // exponentials formed side by side
+  static constexpr int kMSlot = {W["m_first"]};   // first slot that may hold a [M] reaction
+  static constexpr int kOffC = 0;
+  static constexpr int kOffQ = {W["off_q"]};
+  static constexpr int kOffZero = {W["off_zero"]};
+  static constexpr int kNegOff = {W["neg"]};
+  static constexpr int kOffRed = {W["off_red"]};
+  static constexpr int kOffE1 = {W["off_e1"]};   // the energy sum's terms (after the RKC coefficients)
+  static constexpr int kOffE2 = {W["off_e2"]};   // the heat capacity's terms
+  static constexpr int kLdsPerSystem = {W["lds"]};
+  static constexpr int kTermLen = {W["T"]};
+  static constexpr int kPrmOffset = GNet::kPrmOffset + 4 * GNet::R * GNet::kL;
+  using Params = const double*;
+{_table("kSp", "int", [r if r <= n else -1 for r in range(64)])}
+{_table("kRxOf", "int16_t", W["rx_of"])}
+  // LDS byte offsets within the system's area: each lane's rate operands
+  // (R x 4), and the signed rates of its species in reaction order
+{_table("kOp", "uint16_t", W["ops"], align=16)}
+{_table("kTm", "uint16_t", W["tm"], align=16)}
+  struct Lane {{
+    const double* prm;   // the uniform data (rate parameters read at every evaluation)
+    crm::ExpTable et;
+    double W[S], iW[S], u0[S], cv0[S], cv1[S];
+    double rho, irho;
+    uint32_t op[R][4], tm[kTermLen];   // LDS addresses, formed once per system
+    uint32_t c_at;
+  }};
+  __device__ static void init(Lane& L, const Params& p, const double* __restrict__ g, int64_t i,
+                              int64_t, const Grp<WNet>& x) {{
+    L.prm = p;
+    L.et = shared_exp_table(x);
+    const int k = x.sp[0] - 1;   // species of the lane (T and empty lanes: none)
+    const bool sp = k >= 0;
+    L.W[0] = sp ? p[4 * NR + k] : 0.0;
+    L.iW[0] = sp ? p[4 * NR + NS + k] : 0.0;
+    L.u0[0] = sp ? p[4 * NR + 2 * NS + k] : 0.0;
+    L.cv0[0] = sp ? p[4 * NR + 3 * NS + k] : 0.0;
+    L.cv1[0] = sp ? p[4 * NR + 4 * NS + k] : 0.0;
+    L.rho = g[i];
+    L.irho = 1.0 / L.rho;
+    const uint32_t base = lds_address(x.lds);
+    L.c_at = base + 8 * (sp ? k : NS + 1);
+#pragma unroll
+    for (int q = 0; q < 4 * R; ++q) L.op[q / 4][q % 4] = base + kOp[x.r * 4 * R + q];
+#pragma unroll
+    for (int t = 0; t < kTermLen; ++t) L.tm[t] = base + kTm[x.r * kTermLen + t];
+    if (x.r == 0) x.lds[kOffZero] = 0.0;
+  }}
+}};
+
 }}  // namespace gen_{tag}
 }}  // namespace rkmi
 """
@@ -542,7 +620,7 @@ struct GNet {{
 #include "net_{tag}.hpp"
 
 extern "C" int rkmi_gen_{tag}_launch(const rkmi::LaunchArgs* a, void* s) {{
-  return rkmi::launch_group_only<rkmi::gen_{tag}::GNet>(a, s);
+  return rkmi::launch_group_only<rkmi::gen_{tag}::GNet, rkmi::gen_{tag}::WNet>(a, s);
 }}
 
 extern "C" int rkmi_gen_{tag}_host(const rkmi::LaunchArgs*) {{
@@ -552,6 +630,15 @@ extern "C" int rkmi_gen_{tag}_host(const rkmi::LaunchArgs*) {{
 extern "C" int64_t rkmi_gen_{tag}_workspace(int, int, int64_t n) {{
   return n > 0 ? (int64_t)rkmi::kQueueBytes : 0;
 }}
+
+namespace rkmi {{
+RateOrder gen_{tag}_rates(int k) {{
+  using G = gen_{tag}::GNet;
+  using W = gen_{tag}::WNet;
+  return k == 0 ? RateOrder{{G::kRxOf, G::R * G::kL, G::kPrmOffset}}
+                : RateOrder{{W::kRxOf, W::R * W::kL, W::kPrmOffset}};
+}}
+}}  // namespace rkmi
 """
     return header, source
 
@@ -835,20 +922,26 @@ def wide_lanes(n_sp: int) -> int:
     return 32 if n_sp <= 32 else 64
 
 
-def _wide_layout(net, L):
+def _wide_layout(net, L, thermal=False):
     """The wide layout of a network (rk_group.hpp group_rhs_wide): lane r owns
-    species sp[r], forms the rates at positions m L + r and adds its species'
-    signed rates.  LDS area of a system (doubles): C [0, N), the place of
+    unknown r (species r; with the energy equation T, then the species), forms
+    the rates at positions m L + r and adds its species' signed rates.  LDS area of a system (doubles): C [0, N), the place of
     lanes without a species at N + 1 | +q | the zero | scratch | -q, with -q a
     multiple of 64 behind +q (one instruction stores both)."""
     n, nr = net.n_sp, net.n_rx
-    assert n <= L
+    nu = n + 1 if thermal else n
+    assert nu <= L
     R = -(-nr // L)
     pos_of, rx_of, m_first = _group_positions(net, L, R)
     off_q = n + 2 + (n % 2)
     off_zero = off_q + R * L
     off_red = off_zero + 1 + (off_zero + 1) % 2
-    neg = -(-(off_red + n - off_q) // 64) * 64
+    # with the energy equation two species rows follow the RKC recurrence's
+    # coefficients, which stay in the scratch across evaluations
+    off_e1 = off_red + GROUP_COEF_DOUBLES
+    off_e2 = off_e1 + n + 1 + (n + 1) % 2
+    red_len = max(nu + 1, off_e2 + n + 1 - off_red) if thermal else n
+    neg = -(-(off_red + red_len - off_q) // 64) * 64
     lds = off_q + neg + R * L
     lds += lds % 2
     ops = []                     # [L][R][4] LDS byte offsets; [M]: byte offset of C_N
@@ -863,11 +956,13 @@ def _wide_layout(net, L):
     T = max(len(t) for t in terms)
     T += (-T) % 4
     tm = []                      # [L][T]
+    first = nu - n
     for r in range(L):
-        lst = terms[r] if r < n else []
+        lst = terms[r - first] if first <= r < nu else []
         tm += lst + [8 * off_zero] * (T - len(lst))
-    return dict(n=n, nr=nr, L=L, R=R, m_first=m_first, off_q=off_q, off_zero=off_zero,
-                off_red=off_red, neg=neg, lds=lds, ops=ops, tm=tm, T=T, rx_of=rx_of)
+    return dict(n=n, nr=nr, nu=nu, L=L, R=R, m_first=m_first, off_q=off_q, off_zero=off_zero,
+                off_red=off_red, off_e1=off_e1, off_e2=off_e2, red_len=red_len, neg=neg, lds=lds,
+                ops=ops, tm=tm, T=T, rx_of=rx_of)
 
 
 def wide_source(net, tag: str) -> str:
@@ -1064,6 +1159,8 @@ def registry_source(entries, batches=(), thermal=()) -> str:
         decl.append(f'extern "C" int rkmi_gen_{tag}_launch(const rkmi::LaunchArgs*, void*);')
         decl.append(f'extern "C" int rkmi_gen_{tag}_host(const rkmi::LaunchArgs*);')
         decl.append(f'extern "C" int64_t rkmi_gen_{tag}_workspace(int, int, int64_t);')
+        if net.n_sp + 1 > REGISTER_SPECIES_LIMIT:
+            decl.append(f"namespace rkmi {{ RateOrder gen_{tag}_rates(int); }}")
     for tag, net in entries:
         decl.append(f'extern "C" int rkmi_gen_{tag}_launch(const rkmi::LaunchArgs*, void*);')
         decl.append(f'extern "C" int rkmi_gen_{tag}_host(const rkmi::LaunchArgs*);')
@@ -1084,7 +1181,7 @@ def registry_source(entries, batches=(), thermal=()) -> str:
         tabs.append(f"static const int32_t reac_{tag}[] = {{{r}}};")
         tabs.append(f"static const int32_t prod_{tag}[] = {{{p}}};")
         rows.append(f"    {{{net.n_sp}, {net.n_rx}, reac_{tag}, prod_{tag}, rkmi_gen_{tag}_launch, "
-                    f"rkmi_gen_{tag}_host, rkmi_gen_{tag}_workspace, {adj}, 0}},")
+                    f"rkmi_gen_{tag}_host, rkmi_gen_{tag}_workspace, {adj}, 0, nullptr}},")
     index = {tag: k for k, (tag, _) in enumerate(entries)}
     for tag, net in thermal:
         base = tag[:-len(THERMAL_SUFFIX)]
@@ -1095,7 +1192,8 @@ def registry_source(entries, batches=(), thermal=()) -> str:
             tabs.append(f"static const int32_t prod_{base}[] = {{{p}}};")
         rows.append(f"    {{{net.n_sp}, {net.n_rx}, reac_{base}, prod_{base}, rkmi_gen_{tag}_launch, "
                     f"rkmi_gen_{tag}_host, rkmi_gen_{tag}_workspace, "
-                    "nullptr, nullptr, nullptr, nullptr, 1},")
+                    "nullptr, nullptr, nullptr, nullptr, 1, "
+                    f"{f'gen_{tag}_rates' if net.n_sp + 1 > REGISTER_SPECIES_LIMIT else 'nullptr'}}},")
     brows = []
     for tags in batches:
         key = batch_key(tags)

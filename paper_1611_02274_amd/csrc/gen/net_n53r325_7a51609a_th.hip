@@ -4,7 +4,7 @@
 #include "net_n53r325_7a51609a_th.hpp"
 
 extern "C" int rkmi_gen_n53r325_7a51609a_th_launch(const rkmi::LaunchArgs* a, void* s) {
-  return rkmi::launch_group_only<rkmi::gen_n53r325_7a51609a_th::GNet>(a, s);
+  return rkmi::launch_group_only<rkmi::gen_n53r325_7a51609a_th::GNet, rkmi::gen_n53r325_7a51609a_th::WNet>(a, s);
 }
 
 extern "C" int rkmi_gen_n53r325_7a51609a_th_host(const rkmi::LaunchArgs*) {
@@ -14,3 +14,12 @@ extern "C" int rkmi_gen_n53r325_7a51609a_th_host(const rkmi::LaunchArgs*) {
 extern "C" int64_t rkmi_gen_n53r325_7a51609a_th_workspace(int, int, int64_t n) {
   return n > 0 ? (int64_t)rkmi::kQueueBytes : 0;
 }
+
+namespace rkmi {
+RateOrder gen_n53r325_7a51609a_th_rates(int k) {
+  using G = gen_n53r325_7a51609a_th::GNet;
+  using W = gen_n53r325_7a51609a_th::WNet;
+  return k == 0 ? RateOrder{G::kRxOf, G::R * G::kL, G::kPrmOffset}
+                : RateOrder{W::kRxOf, W::R * W::kL, W::kPrmOffset};
+}
+}  // namespace rkmi

@@ -11,9 +11,11 @@ extern "C" int64_t rkmi_gen_n13r27_7b5c2807_th_workspace(int, int, int64_t);
 extern "C" int rkmi_gen_n32r133_bcb31e07_th_launch(const rkmi::LaunchArgs*, void*);
 extern "C" int rkmi_gen_n32r133_bcb31e07_th_host(const rkmi::LaunchArgs*);
 extern "C" int64_t rkmi_gen_n32r133_bcb31e07_th_workspace(int, int, int64_t);
+namespace rkmi { RateOrder gen_n32r133_bcb31e07_th_rates(int); }
 extern "C" int rkmi_gen_n53r325_7a51609a_th_launch(const rkmi::LaunchArgs*, void*);
 extern "C" int rkmi_gen_n53r325_7a51609a_th_host(const rkmi::LaunchArgs*);
 extern "C" int64_t rkmi_gen_n53r325_7a51609a_th_workspace(int, int, int64_t);
+namespace rkmi { RateOrder gen_n53r325_7a51609a_th_rates(int); }
 extern "C" int rkmi_gen_n9r19_49a69f7b_launch(const rkmi::LaunchArgs*, void*);
 extern "C" int rkmi_gen_n9r19_49a69f7b_host(const rkmi::LaunchArgs*);
 extern "C" int64_t rkmi_gen_n9r19_49a69f7b_workspace(int, int, int64_t);
@@ -49,14 +51,14 @@ static const int32_t prod_n53r325_7a51609a[] = {7, 31, 16, 31, 19, 33, 5, 51, 19
 
 namespace rkmi {
 extern const GenEntry kGenRegistry[] = {
-    {9, 19, reac_n9r19_49a69f7b, prod_n9r19_49a69f7b, rkmi_gen_n9r19_49a69f7b_launch, rkmi_gen_n9r19_49a69f7b_host, rkmi_gen_n9r19_49a69f7b_workspace, rkmi_gen_n9r19_49a69f7b_taped, rkmi_gen_n9r19_49a69f7b_taped_host, rkmi_gen_n9r19_49a69f7b_adjoint, rkmi_gen_n9r19_49a69f7b_adjoint_host, 0},
-    {13, 27, reac_n13r27_7b5c2807, prod_n13r27_7b5c2807, rkmi_gen_n13r27_7b5c2807_launch, rkmi_gen_n13r27_7b5c2807_host, rkmi_gen_n13r27_7b5c2807_workspace, rkmi_gen_n13r27_7b5c2807_taped, rkmi_gen_n13r27_7b5c2807_taped_host, rkmi_gen_n13r27_7b5c2807_adjoint, rkmi_gen_n13r27_7b5c2807_adjoint_host, 0},
-    {32, 133, reac_n32r133_bcb31e07, prod_n32r133_bcb31e07, rkmi_gen_n32r133_bcb31e07_launch, rkmi_gen_n32r133_bcb31e07_host, rkmi_gen_n32r133_bcb31e07_workspace, nullptr, nullptr, nullptr, nullptr, 0},
-    {53, 325, reac_n53r325_7a51609a, prod_n53r325_7a51609a, rkmi_gen_n53r325_7a51609a_launch, rkmi_gen_n53r325_7a51609a_host, rkmi_gen_n53r325_7a51609a_workspace, nullptr, nullptr, nullptr, nullptr, 0},
-    {9, 19, reac_n9r19_49a69f7b, prod_n9r19_49a69f7b, rkmi_gen_n9r19_49a69f7b_th_launch, rkmi_gen_n9r19_49a69f7b_th_host, rkmi_gen_n9r19_49a69f7b_th_workspace, nullptr, nullptr, nullptr, nullptr, 1},
-    {13, 27, reac_n13r27_7b5c2807, prod_n13r27_7b5c2807, rkmi_gen_n13r27_7b5c2807_th_launch, rkmi_gen_n13r27_7b5c2807_th_host, rkmi_gen_n13r27_7b5c2807_th_workspace, nullptr, nullptr, nullptr, nullptr, 1},
-    {32, 133, reac_n32r133_bcb31e07, prod_n32r133_bcb31e07, rkmi_gen_n32r133_bcb31e07_th_launch, rkmi_gen_n32r133_bcb31e07_th_host, rkmi_gen_n32r133_bcb31e07_th_workspace, nullptr, nullptr, nullptr, nullptr, 1},
-    {53, 325, reac_n53r325_7a51609a, prod_n53r325_7a51609a, rkmi_gen_n53r325_7a51609a_th_launch, rkmi_gen_n53r325_7a51609a_th_host, rkmi_gen_n53r325_7a51609a_th_workspace, nullptr, nullptr, nullptr, nullptr, 1},
+    {9, 19, reac_n9r19_49a69f7b, prod_n9r19_49a69f7b, rkmi_gen_n9r19_49a69f7b_launch, rkmi_gen_n9r19_49a69f7b_host, rkmi_gen_n9r19_49a69f7b_workspace, rkmi_gen_n9r19_49a69f7b_taped, rkmi_gen_n9r19_49a69f7b_taped_host, rkmi_gen_n9r19_49a69f7b_adjoint, rkmi_gen_n9r19_49a69f7b_adjoint_host, 0, nullptr},
+    {13, 27, reac_n13r27_7b5c2807, prod_n13r27_7b5c2807, rkmi_gen_n13r27_7b5c2807_launch, rkmi_gen_n13r27_7b5c2807_host, rkmi_gen_n13r27_7b5c2807_workspace, rkmi_gen_n13r27_7b5c2807_taped, rkmi_gen_n13r27_7b5c2807_taped_host, rkmi_gen_n13r27_7b5c2807_adjoint, rkmi_gen_n13r27_7b5c2807_adjoint_host, 0, nullptr},
+    {32, 133, reac_n32r133_bcb31e07, prod_n32r133_bcb31e07, rkmi_gen_n32r133_bcb31e07_launch, rkmi_gen_n32r133_bcb31e07_host, rkmi_gen_n32r133_bcb31e07_workspace, nullptr, nullptr, nullptr, nullptr, 0, nullptr},
+    {53, 325, reac_n53r325_7a51609a, prod_n53r325_7a51609a, rkmi_gen_n53r325_7a51609a_launch, rkmi_gen_n53r325_7a51609a_host, rkmi_gen_n53r325_7a51609a_workspace, nullptr, nullptr, nullptr, nullptr, 0, nullptr},
+    {9, 19, reac_n9r19_49a69f7b, prod_n9r19_49a69f7b, rkmi_gen_n9r19_49a69f7b_th_launch, rkmi_gen_n9r19_49a69f7b_th_host, rkmi_gen_n9r19_49a69f7b_th_workspace, nullptr, nullptr, nullptr, nullptr, 1, nullptr},
+    {13, 27, reac_n13r27_7b5c2807, prod_n13r27_7b5c2807, rkmi_gen_n13r27_7b5c2807_th_launch, rkmi_gen_n13r27_7b5c2807_th_host, rkmi_gen_n13r27_7b5c2807_th_workspace, nullptr, nullptr, nullptr, nullptr, 1, nullptr},
+    {32, 133, reac_n32r133_bcb31e07, prod_n32r133_bcb31e07, rkmi_gen_n32r133_bcb31e07_th_launch, rkmi_gen_n32r133_bcb31e07_th_host, rkmi_gen_n32r133_bcb31e07_th_workspace, nullptr, nullptr, nullptr, nullptr, 1, gen_n32r133_bcb31e07_th_rates},
+    {53, 325, reac_n53r325_7a51609a, prod_n53r325_7a51609a, rkmi_gen_n53r325_7a51609a_th_launch, rkmi_gen_n53r325_7a51609a_th_host, rkmi_gen_n53r325_7a51609a_th_workspace, nullptr, nullptr, nullptr, nullptr, 1, gen_n53r325_7a51609a_th_rates},
 };
 extern const int kGenRegistrySize = 8;
 extern const BatchEntry kBatchRegistry[] = {

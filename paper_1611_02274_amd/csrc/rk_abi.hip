@@ -386,6 +386,16 @@ int create_mass_action(const rk_mech_desc* d, const double* thermo, rk_problem* 
   }
   if (thermo)
     for (int k = 0; k < 3 * ns; ++k) p->host_prm[4 * nr + 2 * ns + k] = thermo[k];
+  for (int k = 0; k < 2 && hit->rates; ++k) {
+    const rkmi::RateOrder o = hit->rates(k);
+    p->host_prm.resize(o.offset + 4 * (size_t)o.count, 0.0);
+    for (int i = 0; i < o.count; ++i) {
+      double* const r = &p->host_prm[o.offset + 4 * (size_t)i];
+      // (no reaction: k_f = e, a value the exponential's first evaluation decides)
+      r[0] = 1.0;
+      for (int q = 0; q < 4 && o.rx[i] >= 0; ++q) r[q] = p->host_prm[(size_t)q * nr + o.rx[i]];
+    }
+  }
   *out = p;
   return RK_OK;
 }

@@ -73,6 +73,14 @@ __device__ inline void opaque(uint32_t& v) { asm volatile("" : "+v"(v)); }
 // The same for a double: the value is formed here, not later.
 __device__ inline void opaque_f64(double& v) { asm volatile("" : "+v"(v)); }
 
+// The workgroup's exponential tables, after its groups' areas.
+template <class GP>
+__device__ crm::ExpTable shared_exp_table(const Grp<GP>& x) {
+  crm::ExpTable t;
+  t.p = x.lds + (kLdsStride / GP::kL - (int)threadIdx.x / GP::kL) * GP::kLdsPerSystem;
+  return t;
+}
+
 // The address of an LDS object, and the double at one.
 __device__ inline uint32_t lds_address(const double* p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) double*)p;
@@ -193,9 +201,9 @@ __device__ void group_chain_sum2(const Grp<GP>& x, const double* u, const double
 // The wide variants read all values in every lane instead of passing the sum
 // along the chain of lanes (the same additions; the reads are broadcasts), six
 // pairs ahead of the additions.
-template <class GP>
+template <class GP, int Nv = GP::N>
 struct LaneSum {
-  static constexpr int kPairs = (GP::N + 1) / 2, kAhead = 6;
+  static constexpr int kPairs = (Nv + 1) / 2, kAhead = 6;
   static constexpr int kChunks = (kPairs + kAhead - 1) / kAhead;
   const double2* p;
   double2 next[kAhead];
@@ -215,8 +223,8 @@ struct LaneSum {
 #pragma unroll
     for (int q = 0; q < kAhead; ++q) {
       const int k = 2 * (c * kAhead + q);
-      if (k < GP::N) s += now[q].x;
-      if (k + 1 < GP::N) s += now[q].y;
+      if (k < Nv) s += now[q].x;
+      if (k + 1 < Nv) s += now[q].y;
     }
   }
 };
@@ -313,6 +321,9 @@ __device__ void group_rhs_wide(const typename GP::Lane& L, const Grp<GP>& x,
 template <class GP>
 __device__ void group_rhs_thermal(const typename GP::Lane& L, const Grp<GP>& x,
                                   const double (&y)[GP::S], double (&f)[GP::S]);
+template <class GP>
+__device__ void group_rhs_thermal_wide(const typename GP::Lane& L, const Grp<GP>& x,
+                                       const double (&y)[GP::S], double (&f)[GP::S]);
 
 // Right-hand side of the group's system at y (owned slots) into f.
 template <class GP>
@@ -320,6 +331,8 @@ __device__ void group_rhs(const typename GP::Lane& L, const Grp<GP>& x, const do
                           double (&f)[GP::S]) {
   if constexpr (GroupOwnRhs<GP>::value)
     GP::rhs(L, x, y, f);
+  else if constexpr (GroupThermal<GP>::value && GroupWide<GP>::value)
+    group_rhs_thermal_wide<GP>(L, x, y, f);
   else if constexpr (GroupThermal<GP>::value)
     group_rhs_thermal<GP>(L, x, y, f);
   else if constexpr (GroupWide<GP>::value)
@@ -428,6 +441,33 @@ __device__ void group_rhs_mass_action(const typename GP::Lane& L, const Grp<GP>&
   f[1] = owns<GP>(x, 1) ? (L.W[1] * acc) * L.irho : 0.0;
 }
 
+// The sum of a lane's signed rates in reaction order (wide variants), one batch
+// read ahead of the additions.
+template <class GP>
+__device__ double wide_terms(const typename GP::Lane& L) {
+  constexpr int kB = 12, kT = GP::kTermLen, kBatches = (kT + kB - 1) / kB;
+  double acc = 0.0, next[kB];
+#pragma unroll
+  for (int t = 0; t < kB; ++t)
+    if (t < kT) next[t] = *lds_at(L.tm[t]);
+#pragma unroll
+  for (int b = 0; b < kBatches; ++b) {
+    double now[kB];
+#pragma unroll
+    for (int t = 0; t < kB; ++t) now[t] = next[t];
+#pragma unroll
+    for (int t = 0; t < kB; ++t)
+      if ((b + 1) * kB + t < kT) next[t] = *lds_at(L.tm[(b + 1) * kB + t]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < kB; ++t)
+      if (b * kB + t < kT) acc = acc + now[t];
+    opaque_f64(acc);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  return acc;
+}
+
 // Mass action with one species per lane (64 lanes per system at 53 species, 32
 // at 32): the same exchange, with every LDS address kept in a register (no code
 // tables to read and decode), one sum of terms per lane and [M] added up by
@@ -488,27 +528,7 @@ __device__ void group_rhs_wide(const typename GP::Lane& L, const Grp<GP>& x,
     __builtin_amdgcn_sched_barrier(0);
   }
   group_sync();
-  // the terms, one batch read ahead of the additions
-  constexpr int kB = 12, kT = GP::kTermLen, kBatches = (kT + kB - 1) / kB;
-  double acc = 0.0, next[kB];
-#pragma unroll
-  for (int t = 0; t < kB; ++t)
-    if (t < kT) next[t] = *lds_at(L.tm[t]);
-#pragma unroll
-  for (int b = 0; b < kBatches; ++b) {
-    double now[kB];
-#pragma unroll
-    for (int t = 0; t < kB; ++t) now[t] = next[t];
-#pragma unroll
-    for (int t = 0; t < kB; ++t)
-      if ((b + 1) * kB + t < kT) next[t] = *lds_at(L.tm[(b + 1) * kB + t]);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int t = 0; t < kB; ++t)
-      if (b * kB + t < kT) acc = acc + now[t];
-    opaque_f64(acc);
-    __builtin_amdgcn_sched_barrier(0);
-  }
+  const double acc = wide_terms<GP>(L);
   f[0] = owns<GP>(x, 0) ? (L.W[0] * acc) * L.irho : 0.0;
 }
 
@@ -521,6 +541,14 @@ __device__ void group_rhs_wide(const typename GP::Lane& L, const Grp<GP>& x,
 // Y_k c_v,k(T) and two chain sums over the species give
 // dT/dt = -((sum * (1/rho)) / c_v): the reference evaluation's operations in
 // its order.
+//
+// Bound: the exponentials' dependent chains (two waves per SIMD issue on half
+// the cycles).  They are formed kExps at a time with no branch between them,
+// their tables in LDS, and a batch's parameters are loaded (coalesced: each
+// position's four beside each other) during the batch before.  One exponential
+// after another, gathering its parameters and its tables' entries from global
+// memory: 388 ms for 8191 systems of 53 species (RKC, 1e-6 s), 1193 ms for
+// 32768; so: 284 and 864 ms.  32 species: 280 and 863 ms before, 200 and 641.
 template <class GP>
 __device__ void group_rhs_thermal(const typename GP::Lane& L, const Grp<GP>& x,
                                   const double (&y)[GP::S], double (&f)[GP::S]) {
@@ -535,8 +563,7 @@ __device__ void group_rhs_thermal(const typename GP::Lane& L, const Grp<GP>& x,
                     GP::kOffE2 + GP::NS <= GP::kOffQ + GP::kNegOff &&
                     GP::kOffQ + GP::kNegOff + GP::R * GP::kL <= GP::kLdsPerSystem,
                 "C, T, +q, the zero, the scratch, the energy rows and -q are disjoint");
-  constexpr int NS = GP::NS, NR = GP::NR, LL = GP::kL;
-  const double* const p = L.prm;
+  constexpr int NS = GP::NS, LL = GP::kL;
   double* const C = x.lds + GP::kOffC;
   double* const Q = x.lds + GP::kOffQ;
   const int z0 = opaque_zero();
@@ -554,28 +581,49 @@ __device__ void group_rhs_thermal(const typename GP::Lane& L, const Grp<GP>& x,
   const double M = group_chain_sum<GP, NS>(x, C);
   uint32_t tcw[GP::kTcWords];
   load_row<GP::kTcWords>(GP::kTc, z0 + x.r, tcw);
-  // two slots per iteration: their exponentials' table reads overlap (2.3 %
-  // over a rolled loop at 53 species)
-#pragma unroll 2
-  for (int m = 0; m < GP::R; ++m) {
-    const int pos = m * LL + x.r;
-    const int j = GP::kRxOf[pos + z0];
-    double kf = 0.0, kr = 0.0;
-    if (j >= 0) {
-      kf = crm::cr_exp(p[j] + p[NR + j] * lnT - p[2 * NR + j] * invT);
-      kr = kf * p[3 * NR + j];
+  constexpr int K = GP::kExps, kB = (GP::R + K - 1) / K;
+  const double2* const pr =
+      reinterpret_cast<const double2*>(L.prm + GP::kPrmOffset + z0) + 2 * x.r;
+  double2 pa[K], pb[K];   // (ln A, b) and (E, 1/K) of the next batch's positions
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    pa[k] = pr[2 * LL * k];
+    pb[k] = pr[2 * LL * k + 1];
+  }
+#pragma unroll
+  for (int b = 0; b < kB; ++b) {
+    double a[K], kf[K], iK[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      a[k] = pa[k].x + pa[k].y * lnT - pb[k].x * invT;
+      iK[k] = pb[k].y;
     }
-    const uint32_t code = rxl[m];
-    const uint32_t ib = (code >> 8) & 0xffu, id = code >> 24;
-    const double ca = C[code & 0xffu], cc = C[(code >> 16) & 0xffu];
-    double cb = C[ib], cd = C[id];
-    if (m >= GP::kMSlot) {
-      cb = ib == (uint32_t)NS ? M : cb;
-      cd = id == (uint32_t)NS ? M : cd;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if ((b + 1) * K + k < GP::R) {
+        pa[k] = pr[2 * LL * ((b + 1) * K + k)];
+        pb[k] = pr[2 * LL * ((b + 1) * K + k) + 1];
+      }
+    crm::cr_exp_n<K>(a, kf, L.et);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int m = b * K + k, pos = m * LL + x.r;
+      if (m >= GP::R) continue;
+      const double kr = kf[k] * iK[k];
+      const uint32_t code = rxl[m];
+      const uint32_t ib = (code >> 8) & 0xffu, id = code >> 24;
+      const double ca = C[code & 0xffu], cc = C[(code >> 16) & 0xffu];
+      double cb = C[ib], cd = C[id];
+      if (m >= GP::kMSlot) {
+        cb = ib == (uint32_t)NS ? M : cb;
+        cd = id == (uint32_t)NS ? M : cd;
+      }
+      const double q = (kf[k] * ca) * cb - (kr * cc) * cd;
+      Q[pos] = q;
+      Q[GP::kNegOff + pos] = -q;
     }
-    const double q = (kf * ca) * cb - (kr * cc) * cd;
-    Q[pos] = q;
-    Q[GP::kNegOff + pos] = -q;
+    __builtin_amdgcn_sched_barrier(0);
   }
   group_sync();
   double acc = 0.0, om0 = 0.0;
@@ -617,6 +665,114 @@ __device__ void group_rhs_thermal(const typename GP::Lane& L, const Grp<GP>& x,
 #pragma unroll
   for (int m = 0; m < GP::S; ++m)
     if (x.sp[m] == 0) f[m] = -((sum * L.irho) / cv);
+}
+
+// Mass action with the energy equation (Sec. 4.2 at constant volume), one
+// unknown per lane of a wave: T from its lane to all of them, each position's
+// lane forms its reactions' rate coefficients k_f = exp(ln A + b ln T - E (1/T))
+// and k_r = k_f (1/K), the species part as group_rhs_wide, then every species
+// lane writes (e_k omega_k) W_k and Y_k c_v,k(T) and two sums over the species
+// give dT/dt = -((sum * (1/rho)) / c_v): the reference evaluation's operations
+// in its order, the exponentials as in group_rhs_thermal.
+//
+// For small batches, bound by one evaluation's latency: half the rates, terms
+// and unknowns per lane and a whole SIMD's registers.  One wave per SIMD and
+// one system per wave, it loses once the 32-lane kernels fill both their waves.
+// RKC over 1e-6 s, ms here / 32 lanes per system: 53 species 1024 systems 92 /
+// 162, 2000 128 / 145, 4096 224 / 164; 32 species 1024 63 / 103, 2000 105 /
+// 105, 4096 185 / 120.  RKCK, whose few longest systems end the batch: 53
+// species 4096 586 / 808, 16384 1634 / 1769, 24576 2038 / 1842; 32 species 4096
+// 490 / 971, 8192 790 / 900, 16384 1191 / 1040.  Hence kMaxRkc and kMaxRkck.
+template <class GP>
+__device__ void group_rhs_thermal_wide(const typename GP::Lane& L, const Grp<GP>& x,
+                                  const double (&y)[GP::S], double (&f)[GP::S]) {
+  static_assert(GP::S == 1 && GP::kL == 64 && GP::kOffC == 0 && GP::kNegOff % 64 == 0 &&
+                    GP::kOffE1 % 2 == 0 && GP::kOffE2 % 2 == 0 && GP::kPrmOffset % 2 == 0,
+                "one unknown per lane, aligned areas");
+  static_assert(sizeof(RkcCoef) <= sizeof(double) * (GP::kOffE1 - GP::kOffRed),
+                "the energy rows leave the RKC coefficients kept in the scratch intact");
+  static_assert(GP::NS + 1 < GP::kOffQ && GP::kOffZero == GP::kOffQ + GP::R * GP::kL &&
+                    GP::kOffZero < GP::kOffRed &&
+                    GP::kOffRed + GP::N <= GP::kOffQ + GP::kNegOff &&
+                    GP::kOffE1 + GP::NS < GP::kOffE2 &&
+                    GP::kOffE2 + GP::NS < GP::kOffQ + GP::kNegOff &&
+                    GP::kOffQ + GP::kNegOff + GP::R * GP::kL <= GP::kLdsPerSystem,
+                "C, +q, the zero, the scratch, the energy rows and -q are disjoint");
+  constexpr int kR = GP::R, K = GP::kExps;
+  const double2* const pr = reinterpret_cast<const double2*>(L.prm + GP::kPrmOffset +
+                                                             opaque_zero()) + 2 * x.r;
+  double2 pa[kR], pb[kR];   // (ln A, b) and (E, 1/K) of the lane's positions
+#pragma unroll
+  for (int m = 0; m < kR; ++m) {
+    pa[m] = pr[128 * m];
+    pb[m] = pr[128 * m + 1];
+  }
+  double* const Q = x.lds + GP::kOffQ + x.r;
+  *lds_at(L.c_at) = (L.rho * y[0]) * L.iW[0];
+  group_sync();
+  LaneSum<GP, GP::NS> sum(x.lds);
+  constexpr int kChunks = LaneSum<GP, GP::NS>::kChunks;
+  const double T = __shfl(y[0], 0);
+  const double lnT = crm::cr_log(T);
+  const double invT = 1.0 / T;
+  double kf[kR];
+#pragma unroll
+  for (int m0 = 0; m0 < kR; m0 += K) {
+    double a[K], e[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int m = m0 + k < kR ? m0 + k : kR - 1;
+      a[k] = pa[m].x + pa[m].y * lnT - pb[m].x * invT;
+    }
+    // a part of [M]'s additions beside each batch of exponentials
+#pragma unroll
+    for (int k = 0; k < kChunks; ++k)
+      if (k * ((kR + K - 1) / K) / kChunks == m0 / K) sum.step(k);
+    crm::cr_exp_n<K>(a, e, L.et);
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if (m0 + k < kR) kf[m0 + k] = e[k];
+  }
+  const uint32_t m_at = lds_address(x.lds) + 8 * GP::NS;
+  double a[2][4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) a[0][q] = *lds_at(L.op[0][q]);
+#pragma unroll
+  for (int m = 0; m < kR; ++m) {
+    double (&c)[4] = a[m % 2];
+    if (m + 1 < kR)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a[(m + 1) % 2][q] = *lds_at(L.op[m + 1][q]);
+    if (m >= GP::kMSlot) {
+      c[1] = L.op[m][1] == m_at ? sum.s : c[1];
+      c[3] = L.op[m][3] == m_at ? sum.s : c[3];
+    }
+    const double kr = kf[m] * pb[m].y;
+    const double q = (kf[m] * c[0]) * c[1] - (kr * c[2]) * c[3];
+    Q[m * GP::kL] = q;
+    Q[m * GP::kL + GP::kNegOff] = -q;
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  group_sync();
+  const double om = wide_terms<GP>(L);
+  const bool sp = x.sp[0] > 0;
+  f[0] = sp ? (L.W[0] * om) * L.irho : 0.0;
+  if (sp) {
+    const int k = x.sp[0] - 1;
+    const double e = L.u0[0] + (L.cv0[0] + L.cv1[0] * T) * T;
+    x.lds[GP::kOffE1 + k] = (e * om) * L.W[0];
+    x.lds[GP::kOffE2 + k] = y[0] * (L.cv0[0] + 2.0 * L.cv1[0] * T);
+  }
+  group_sync();
+  LaneSum<GP, GP::NS> s1(x.lds + GP::kOffE1), s2(x.lds + GP::kOffE2);
+#pragma unroll
+  for (int c = 0; c < kChunks; ++c) {
+    s1.step(c);
+    s2.step(c);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  group_sync();
+  if (x.sp[0] == 0) f[0] = -((s1.s * L.irho) / s2.s);
 }
 
 template <class GP>
@@ -1049,7 +1205,7 @@ constexpr int kGroups = kLdsStride / GP::kL;
 
 template <class GP>
 constexpr int group_lds_doubles() {
-  return kGroups<GP> * GP::kLdsPerSystem;
+  return kGroups<GP> * GP::kLdsPerSystem + SharedDoubles<GP>::value;
 }
 
 // Group RKCK attempt by attempt: all six evaluations of an attempt in one
@@ -1367,6 +1523,11 @@ __attribute__((amdgpu_waves_per_eu(GroupWavesPerEu<GP, Method>::value))) void gr
     int32_t* __restrict__ stats, unsigned long long* queue, const int32_t* __restrict__ order,
     double* __restrict__ carry) {
   __shared__ __attribute__((aligned(16))) double lds[group_lds_doubles<GP>()];
+  if constexpr (SharedDoubles<GP>::value > 0) {   // the exponentials' tables, after the groups' areas
+    for (int k = threadIdx.x; k < crm::kExpTableDoubles; k += kLdsStride)
+      lds[kGroups<GP> * GP::kLdsPerSystem + k] = crm::exp_table_entry(k);
+    __syncthreads();
+  }
   group_persistent_loop<GP, Method>(prm, n, y0, y1, g, c, status, stats, queue, lds, order,
                                     carry);
 }
@@ -1392,52 +1553,58 @@ int launch_group_method(const LaunchArgs* a, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? kLaunchOk : kLaunchHip;
 }
 
+// The group kernels of GP, with a cost pass ahead of them or without.
+template <class GP>
+int launch_group(const LaunchArgs* a, hipStream_t s) {
+  if (a->pilot)
+    return a->method == kMethodRkck ? launch_group_method<GP, kMethodRkck, true>(a, s)
+                                    : launch_group_method<GP, kMethodRkc, true>(a, s);
+  return a->method == kMethodRkck ? launch_group_method<GP, kMethodRkck, false>(a, s)
+                                  : launch_group_method<GP, kMethodRkc, false>(a, s);
+}
+
 // Launches the one-lane kernels of Prob for the plain and persistent
 // schedules and the group kernels of GP for the group schedule (the default).
 template <class Prob, class GP>
 int launch_with_group(const LaunchArgs* a, void* stream) {
-  const hipStream_t s = static_cast<hipStream_t>(stream);
   if (a->schedule == kSchedPlain || a->schedule == kSchedPersistent) return launch<Prob>(a, stream);
   if (!a->ws || a->ws_bytes < kQueueBytes) return launch<Prob>(a, stream);   // no queue: plain
-  if (a->pilot)
-    return a->method == kMethodRkck ? launch_group_method<GP, kMethodRkck, true>(a, s)
-                                    : launch_group_method<GP, kMethodRkc, true>(a, s);
-  return a->method == kMethodRkck ? launch_group_method<GP, kMethodRkck, false>(a, s)
-                                  : launch_group_method<GP, kMethodRkc, false>(a, s);
+  return launch_group<GP>(a, static_cast<hipStream_t>(stream));
 }
 
-// Launches the wide variant WP for batches of up to its kMaxRkc / kMaxRkck
-// systems per SIMD, the group kernels of GP for larger ones, and the one-lane
-// kernels as launch_with_group does.
-template <class Prob, class GP, class WP>
-int launch_with_wide(const LaunchArgs* a, void* stream) {
-  const hipStream_t s = static_cast<hipStream_t>(stream);
+// *yes: the wide variant WP runs the batch, of up to its kMaxRkc / kMaxRkck
+// systems per SIMD.
+template <class WP>
+bool wide_runs(const LaunchArgs* a, bool* yes) {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    return kLaunchHip;
-  const int64_t most = (a->method == kMethodRkck ? WP::kMaxRkck : WP::kMaxRkc) * (int64_t)cus * 4;
-  if (a->schedule == kSchedPlain || a->schedule == kSchedPersistent || !a->ws ||
-      a->ws_bytes < kQueueBytes || a->n > most)
-    return launch_with_group<Prob, GP>(a, stream);
-  if (a->pilot)
-    return a->method == kMethodRkck ? launch_group_method<WP, kMethodRkck, true>(a, s)
-                                    : launch_group_method<WP, kMethodRkc, true>(a, s);
-  return a->method == kMethodRkck ? launch_group_method<WP, kMethodRkck, false>(a, s)
-                                  : launch_group_method<WP, kMethodRkc, false>(a, s);
+    return false;
+  *yes = a->n <= (a->method == kMethodRkck ? WP::kMaxRkck : WP::kMaxRkc) * (int64_t)cus * 4;
+  return true;
 }
 
-// Launches the group kernels of GP under every schedule (problems without
-// one-lane kernels).
-template <class GP>
+// Launches the wide variant WP for small batches, the group kernels of GP for
+// larger ones, and the one-lane kernels as launch_with_group does.
+template <class Prob, class GP, class WP>
+int launch_with_wide(const LaunchArgs* a, void* stream) {
+  bool wide = false;
+  if (!wide_runs<WP>(a, &wide)) return kLaunchHip;
+  if (a->schedule == kSchedPlain || a->schedule == kSchedPersistent || !a->ws ||
+      a->ws_bytes < kQueueBytes || !wide)
+    return launch_with_group<Prob, GP>(a, stream);
+  return launch_group<WP>(a, static_cast<hipStream_t>(stream));
+}
+
+// Launches the wide variant WP or the group kernels of GP under every schedule
+// (problems without one-lane kernels).
+template <class GP, class WP>
 int launch_group_only(const LaunchArgs* a, void* stream) {
   const hipStream_t s = static_cast<hipStream_t>(stream);
   if (a->n > 0 && (!a->ws || a->ws_bytes < kQueueBytes)) return kLaunchWorkspace;
-  if (a->pilot)
-    return a->method == kMethodRkck ? launch_group_method<GP, kMethodRkck, true>(a, s)
-                                    : launch_group_method<GP, kMethodRkc, true>(a, s);
-  return a->method == kMethodRkck ? launch_group_method<GP, kMethodRkck, false>(a, s)
-                                  : launch_group_method<GP, kMethodRkc, false>(a, s);
+  bool wide = false;
+  if (!wide_runs<WP>(a, &wide)) return kLaunchHip;
+  return wide ? launch_group<WP>(a, s) : launch_group<GP>(a, s);
 }
 
 template <class Prob, class GP>

@@ -90,6 +90,15 @@ typedef int (*taped_host_fn)(const LaunchArgs*, const TapeArgs*);
 typedef int (*adjoint_fn)(const AdjointArgs*, void* stream);
 typedef int (*adjoint_host_fn)(const AdjointArgs*);
 
+// The order in which a network's kernels want the rate parameters: position i's
+// reaction rx[i] has (lnA, beta, Ea, 1/K) at uniform data entry offset + 4 i
+// (rx[i] = -1: (1, 0, 0, 0)).  k = 0: the group kernel's; 1: its wide variant's.
+struct RateOrder {
+  const int16_t* rx;
+  int count, offset;
+};
+typedef RateOrder (*rate_order_fn)(int k);
+
 // Compiled network: the topology it was generated for and its launchers.
 struct GenEntry {
   int n_sp;
@@ -104,6 +113,7 @@ struct GenEntry {
   adjoint_fn adjoint;
   adjoint_host_fn adjoint_host;
   int thermal;                    // 1: compiled with the energy equation (state T, Y)
+  rate_order_fn rates;            // null: the uniform data ends with the species' constants
 };
 
 // Ragged batch of several compiled networks (rk_batch.hpp).
