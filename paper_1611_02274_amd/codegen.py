@@ -18,6 +18,7 @@ constants are multiplications by reciprocals formed once.
 from __future__ import annotations
 
 import os
+import random
 
 import numpy as np
 
@@ -503,9 +504,6 @@ struct GNet {{
   static constexpr int kOffE1 = {G["off_e1"]};   // the energy sum's terms (after the RKC coefficients)
   static constexpr int kOffE2 = {G["off_e2"]};   // the heat capacity's terms
   static constexpr int kLdsPerSystem = {G["lds_per_system"]};
-  static constexpr int kTermBits = {G["bits"]};
-  static constexpr int kTermsPerWord = {G["per_word"]};
-  static constexpr int kTermWords = {G["n_words"]};
   static constexpr int kTermLen = {G["tot"]};
   static constexpr int kChunk = {G["chunk"]};
   // uniform data: [lnA | beta | Ea | 1/K | W | 1/W | u0 | cv0 | cv1], then (lnA,
@@ -547,8 +545,8 @@ struct WNet {{
   static constexpr bool kThermal = true;
   static constexpr bool kWide = true;
   // largest batches it runs, in systems per SIMD (rk_group.hpp group_rhs_thermal_wide)
-  static constexpr int kMaxRkck = {8 if n <= 32 else 16};
-  static constexpr int kMaxRkc = {1 if n <= 32 else 2};
+  static constexpr int kMaxRkck = {6 if n <= 32 else 12};
+  static constexpr int kMaxRkc = 1;
   static constexpr bool kExpTable = true;
   static constexpr int NS = {n};
   static constexpr int N = NS + 1;    // unknowns: T, then the species
@@ -701,6 +699,71 @@ def _group_positions(net, L, R):
     return pos_of, rx_of, (m_first if third else R)
 
 
+def _spread_banks(net, L, R, m_first, pos_of, rx_of, seqs, neg, off_q, zero, area):
+    """Rearranges the reactions over their positions, within the slots before
+    m_first and those from it on, so that a wave's reads of LDS meet in fewer
+    banks: a 64-lane read of doubles takes the sum over its two halves of the
+    most addresses in one of the 32 banks (measured: 3.1 cycles at one each, 4.6
+    at two, 8.5 at four).  seqs[r] is the sequence of lane r's terms ((reaction,
+    1 if negative) or None, the zero at `zero`), area the doubles of a system; a
+    deterministic local search."""
+    rng = random.Random(1)
+    steps = max(len(q) for q in seqs)
+    reads = steps + 4 * R           # the terms' reads, then the operands'
+    refs = [({}, {}) for _ in range(reads)]
+    load = [([0] * 32, [0] * 32) for _ in range(reads)]
+    lanes = [[((g * L + r) // 32, g * area) for g in range(64 // L)] for r in range(L)]
+    species = [[int(k) if k >= 0 else net.n_sp for k in (*net.reac[j], *net.prod[j])]
+               for j in range(net.n_rx)]
+    uses = [[] for _ in range(net.n_rx)]
+
+    def count(i, r, a, d):
+        for h, off in lanes[r]:
+            c = refs[i][h].get(a + off, 0) + d
+            refs[i][h][a + off] = c
+            if c == max(d, 0):      # the address came or went
+                load[i][h][(a + off) % 32] += d
+
+    def place(j, p, d):
+        r, m = p % L, p // L
+        for q in range(4):
+            count(steps + 4 * m + q, r, species[j][q] if j >= 0 else 0, d)
+        for t, rr, minus in uses[j] if j >= 0 else ():
+            count(t, rr, off_q + p + neg * minus, d)
+
+    def cost(i):
+        return max(load[i][0]) + max(load[i][1])
+
+    for r in range(L):
+        for t, e in enumerate(seqs[r]):
+            if e is None:
+                count(t, r, zero, 1)
+            else:
+                uses[e[0]].append((t, r, e[1]))
+    for p, j in enumerate(rx_of):
+        place(j, p, 1)
+    costs = [cost(i) for i in range(reads)]
+    for _ in range(12000):
+        a = rng.randrange(R * L)
+        b = rng.randrange(m_first * L) if a < m_first * L else rng.randrange(m_first * L, R * L)
+        ja, jb = rx_of[a], rx_of[b]
+        if ja == jb:
+            continue
+        place(ja, a, -1), place(jb, b, -1), place(ja, b, 1), place(jb, a, 1)
+        touched = {t for j in (ja, jb) if j >= 0 for t, _, _ in uses[j]}
+        touched |= {steps + 4 * (p // L) + q for p in (a, b) for q in range(4)}
+        after = {i: cost(i) for i in touched}
+        if sum(after.values()) > sum(costs[i] for i in touched):
+            place(ja, b, -1), place(jb, a, -1), place(ja, a, 1), place(jb, b, 1)
+            continue
+        for i, c in after.items():
+            costs[i] = c
+        for j, p in ((ja, b), (jb, a)):
+            rx_of[p] = j
+            if j >= 0:
+                pos_of[j] = p
+
+
 def _group_species(lens, L, chunk):
     """Species -> (lane, slot) for two slots per lane: each lane sums its
     slot-0 species' terms (padded to whole chunks), then its slot-1 species'.
@@ -741,17 +804,6 @@ def _group_layout(net, L, thermal=False):
     assert n < 255, "species indices are packed in bytes"
     chunk = GROUP_TERM_CHUNK
     pos_of, rx_of, m_first = _group_positions(net, L, R)
-    rx = []
-    for p in range(R * L):
-        j = rx_of[p]
-        if j >= 0:
-            a, b = int(net.reac[j][0]), int(net.reac[j][1])
-            c, d = int(net.prod[j][0]), int(net.prod[j][1])
-            b = n if b < 0 else b
-            d = n if d < 0 else d
-            rx.append(a | b << 8 | c << 16 | d << 24)
-        else:
-            rx.append(0)
     # LDS area of a system (doubles): C [0, NS] (C_N the [M] operand's place;
     # with the energy equation T at NS + 1) | rates +q at kOffQ + p, p < R*L,
     # the zero at kOffQ + R*L, scratch (16-byte aligned: the norms over the
@@ -769,7 +821,7 @@ def _group_layout(net, L, thermal=False):
     lds_per_system = off_q + neg + R * L
     lds_per_system += lds_per_system % 2
     sentinel = R * L
-    sterms = [[pos_of[c >> 1] + neg * (c & 1) for c in lst] for lst in _species_terms(net)]
+    sterms = [[(c >> 1, c & 1) for c in lst] for lst in _species_terms(net)]
     terms = ([[]] + sterms) if thermal else sterms     # per unknown
     lens = [len(t) for t in terms]
     sp = _group_species(lens, L, chunk)
@@ -777,14 +829,28 @@ def _group_layout(net, L, thermal=False):
     for r in range(L):
         k0, k1 = sp[r], sp[L + r]
         l0 = terms[k0] if k0 >= 0 else []
-        l0 = l0 + [sentinel] * ((-len(l0)) % chunk)
+        l0 = l0 + [None] * ((-len(l0)) % chunk)
         l1 = terms[k1] if k1 >= 0 else []
         seqs.append(l0 + l1)
         bnd.append(len(l0) // chunk)
     tot = max(len(q) for q in seqs)
     tot += (-tot) % chunk
     assert tot // chunk <= 64
-    seqs = [q + [sentinel] * (tot - len(q)) for q in seqs]
+    seqs = [q + [None] * (tot - len(q)) for q in seqs]
+    _spread_banks(net, L, R, m_first, pos_of, rx_of, seqs, neg, off_q, off_q + sentinel,
+                  lds_per_system)
+    seqs = [[sentinel if e is None else pos_of[e[0]] + neg * e[1] for e in q] for q in seqs]
+    rx = []
+    for p in range(R * L):
+        j = rx_of[p]
+        if j >= 0:
+            a, b = int(net.reac[j][0]), int(net.reac[j][1])
+            c, d = int(net.prod[j][0]), int(net.prod[j][1])
+            b = n if b < 0 else b
+            d = n if d < 0 else d
+            rx.append(a | b << 8 | c << 16 | d << 24)
+        else:
+            rx.append(0)
     bits = (neg + R * L).bit_length()
     per_word = 32 // bits
     n_words = max(1, -(-tot // per_word))
@@ -800,48 +866,57 @@ def _group_layout(net, L, thermal=False):
                 switch=sum(1 << (b - 1) for b in set(bnd) if b > 0))
 
 
-def _lane_major(words, L, per_lane):
-    """A [per_lane][L] table (entry w of lane r at w L + r) as [L][per_lane']
-    with per_lane' = per_lane rounded up to whole 16-byte vectors (zeros)."""
-    padded = -(-per_lane // 4) * 4
-    out = [0] * (L * padded)
-    for r in range(L):
-        for w in range(per_lane):
-            out[r * padded + w] = words[w * L + r]
-    return out, padded
-
-
 def _group_tables(G) -> str:
-    rx, rx_words = _lane_major(G["rx"], G["L"], G["R"])
-    tc, tc_words = _lane_major(G["tc"], G["L"], G["n_words"])
+    op, op_words, tm, tm_words = _packed_addresses(G)
     return f"""{_table("kSp", "int", G["sp"])}
 {_table("kRxOf", "int16_t", G["rx_of"])}
-  // lane r's operand codes and packed term codes, each lane's contiguous and
-  // 16-byte aligned (read as whole vectors at every evaluation)
-  static constexpr int kRxWords = {rx_words};
-  static constexpr int kTcWords = {tc_words};
-{_table("kRx", "uint32_t", rx, align=16)}
-{_table("kTc", "uint32_t", tc, align=16)}
+  // each lane's LDS byte offsets in the wave's areas, two to a word, contiguous
+  // and 16-byte aligned (read as whole vectors at every evaluation): the rates'
+  // operands, the terms
+  static constexpr int kOpWords = {op_words};
+  static constexpr int kTmWords = {tm_words};
+{_table("kOp", "uint32_t", op, align=16)}
+{_table("kTm", "uint32_t", tm, align=16)}
 {_table("kBnd", "int", G["bnd"])}
   // chunks at whose end some lane moves its accumulator to slot 0 (bit c)
   static constexpr uint64_t kSwitchChunks = {G["switch"]}ull;"""
+
+
+def _packed_addresses(G):
+    """Byte offsets in a wave's LDS areas, two to a word, each lane's words
+    contiguous and padded to whole 16-byte vectors: its rate operands (four per
+    slot) and the terms of its species' sums, from the layout's codes.  Returns
+    (operand words, words per lane, term words, words per lane)."""
+    L, R, bits, per_word = G["L"], G["R"], G["bits"], G["per_word"]
+
+    def packed(entry, count):
+        out = []
+        for lane in range(64):
+            v = [8 * (entry(k, lane % L) + lane // L * G["lds_per_system"]) for k in range(count)]
+            assert max(v) < 1 << 16
+            v += [0] * (-count % 8)
+            out += [a | b << 16 for a, b in zip(v[::2], v[1::2])]
+        return out, len(out) // 64
+
+    return (*packed(lambda k, r: G["rx"][k // 4 * L + r] >> (8 * (k % 4)) & 255, 4 * R),
+            *packed(lambda k, r: G["off_q"] + (G["tc"][k // per_word * L + r]
+                                               >> (k % per_word * bits) & ((1 << bits) - 1)),
+                    G["tot"]))
 
 
 def group_source(net, tag: str, lanes: int | None = None) -> str:
     """The group variant of a network (kernels of rk_group.hpp): lane r of a
     group of `lanes` computes the rates of progress at its positions
     p = m*lanes + r (_group_positions) and owns the species of its two slots
-    (_group_species); per lane: the species of each slot, the packed operand
-    species of each position's reaction, and the signed rate positions of its
-    species' sums in reaction order (slot 0's list, padded to whole chunks,
-    then slot 1's), packed into registers."""
+    (_group_species); per lane: the species of each slot, the LDS offsets of
+    each position's operands and those of its species' signed rates in reaction
+    order (slot 0's list, padded to whole chunks, then slot 1's)."""
     n, nr = net.n_sp, net.n_rx
     L = lanes or group_lanes(n)
     G = _group_layout(net, L)
     S, R, m_first = G["S"], G["R"], G["m_first"]
     off_q, sentinel, neg, off_red = G["off_q"], G["sentinel"], G["neg"], G["off_red"]
-    lds_per_system, bits, per_word, n_words = (G["lds_per_system"], G["bits"], G["per_word"],
-                                               G["n_words"])
+    lds_per_system = G["lds_per_system"]
     tot, chunk = G["tot"], G["chunk"]
     return f"""
 // Group variant: {L} lanes per system (rk_group.hpp).
@@ -852,8 +927,8 @@ struct GNet {{
   static constexpr int kGroupLanes = {L};
   static constexpr bool kColumns = false;
   static constexpr int kLaneDoubles = 0;
-  // three waves per SIMD: the evaluation loop fits 168 registers (the power
-  // method and the set-up of a system run out of line)
+  // RKCK: three waves per SIMD, its loop fits 168 registers but for a few spills
+  // outside the evaluations (53 species, 65536 systems: 636 ms, two waves 698)
   static constexpr int kWavesPerEuRkc = 2;
   static constexpr int kWavesPerEuRkck = 3;
   static constexpr int S = {S};
@@ -865,9 +940,6 @@ struct GNet {{
   static constexpr int kNegOff = {neg};
   static constexpr int kOffRed = {off_red};
   static constexpr int kLdsPerSystem = {lds_per_system};
-  static constexpr int kTermBits = {bits};
-  static constexpr int kTermsPerWord = {per_word};
-  static constexpr int kTermWords = {n_words};
   static constexpr int kTermLen = {tot};
   static constexpr int kChunk = {chunk};
   using Params = const double*;
@@ -925,9 +997,10 @@ def wide_lanes(n_sp: int) -> int:
 def _wide_layout(net, L, thermal=False):
     """The wide layout of a network (rk_group.hpp group_rhs_wide): lane r owns
     unknown r (species r; with the energy equation T, then the species), forms
-    the rates at positions m L + r and adds its species' signed rates.  LDS area of a system (doubles): C [0, N), the place of
-    lanes without a species at N + 1 | +q | the zero | scratch | -q, with -q a
-    multiple of 64 behind +q (one instruction stores both)."""
+    the rates at positions m L + r and adds its species' signed rates.  LDS area
+    of a system (doubles): C [0, N), the place of lanes without a species at
+    N + 1 | +q | the zero | scratch | -q, with -q a multiple of 64 behind +q (one
+    instruction stores both)."""
     n, nr = net.n_sp, net.n_rx
     nu = n + 1 if thermal else n
     assert nu <= L
@@ -944,22 +1017,21 @@ def _wide_layout(net, L, thermal=False):
     neg = -(-(off_red + red_len - off_q) // 64) * 64
     lds = off_q + neg + R * L
     lds += lds % 2
+    terms = [[(c >> 1, c & 1) for c in lst] for lst in _species_terms(net)]
+    T = max(len(t) for t in terms)
+    T += (-T) % 4
+    first = nu - n
+    seqs = [terms[r - first] if first <= r < nu else [] for r in range(L)]
+    seqs = [q + [None] * (T - len(q)) for q in seqs]
+    _spread_banks(net, L, R, m_first, pos_of, rx_of, seqs, neg, off_q, off_zero, lds)
     ops = []                     # [L][R][4] LDS byte offsets; [M]: byte offset of C_N
     for r in range(L):
         for m in range(R):
             j = rx_of[m * L + r]
-            a, b = (int(net.reac[j][0]), int(net.reac[j][1])) if j >= 0 else (0, 0)
-            c, d = (int(net.prod[j][0]), int(net.prod[j][1])) if j >= 0 else (0, 0)
-            ops += [8 * (n if k < 0 else k) for k in (a, b, c, d)]
-    terms = [[8 * (off_q + pos_of[c >> 1] + neg * (c & 1)) for c in lst]
-             for lst in _species_terms(net)]
-    T = max(len(t) for t in terms)
-    T += (-T) % 4
-    tm = []                      # [L][T]
-    first = nu - n
-    for r in range(L):
-        lst = terms[r - first] if first <= r < nu else []
-        tm += lst + [8 * off_zero] * (T - len(lst))
+            ops += [8 * (int(k) if k >= 0 else n) if j >= 0 else 0
+                    for k in ((*net.reac[j], *net.prod[j]) if j >= 0 else (0,) * 4)]
+    tm = [8 * (off_zero if e is None else off_q + pos_of[e[0]] + neg * e[1])
+          for q in seqs for e in q]     # [L][T]
     return dict(n=n, nr=nr, nu=nu, L=L, R=R, m_first=m_first, off_q=off_q, off_zero=off_zero,
                 off_red=off_red, off_e1=off_e1, off_e2=off_e2, red_len=red_len, neg=neg, lds=lds,
                 ops=ops, tm=tm, T=T, rx_of=rx_of)
@@ -974,8 +1046,8 @@ def wide_source(net, tag: str) -> str:
 struct WNet {{
   static constexpr bool kWide = true;
   // largest batches it runs, in systems per SIMD (rk_group.hpp group_rhs_wide)
-  static constexpr int kMaxRkck = {64 if n <= 32 else 32};
-  static constexpr int kMaxRkc = {24 if n <= 32 else 2};
+  static constexpr int kMaxRkck = {48 if n <= 32 else 16};
+  static constexpr int kMaxRkc = {6 if n <= 32 else 1};
   static constexpr int N = {n};
   static constexpr int NR = {G["nr"]};
   static constexpr int kL = {G["L"]};

@@ -23,11 +23,10 @@
 // [M]), the LDS layout (kOffC, kOffQ, kSentinel, kNegOff, kOffRed,
 // kLdsPerSystem: +q at kOffQ + p, the zero at kOffQ + kSentinel, -q at
 // kOffQ + kNegOff + p), the tables kSp (species of slot m of lane r at
-// m L + r, -1 for none), kRx (packed operand species of each position's
-// reaction, [M] as index N; lane-major, kRxWords per lane), kTc (each lane's
-// signed rate positions, packed, lane-major, kTcWords per lane:
-// its slot-0 species' list padded with the zero to whole chunks of kChunk
-// terms, then its slot-1 species' list, kTermLen in all), kBnd (the chunks
+// m L + r, -1 for none), kOp and kTm (for each lane of the wave the LDS byte
+// offsets of its rates' operands, C_N standing for [M], and of its terms, two
+// to a word: its slot-0 species' list padded with the zero to whole chunks of
+// kChunk terms, then its slot-1 species' list, kTermLen in all), kBnd (the chunks
 // of the slot-0 list) and kSwitchChunks (the chunks at whose end some lane
 // switches), Params, Lane, init(Lane&, prm, g, i, n, x).
 #pragma once
@@ -49,6 +48,7 @@ template <class GP>
 struct Grp {
   int r;                     // position in the group
   double* lds;               // the group's LDS area
+  uint32_t areas;            // the address of the workgroup's areas
   unsigned long long mask;   // the group's lanes in the wave
   int sp[GP::S];
 };
@@ -66,11 +66,7 @@ struct GroupWide<GP, std::void_t<decltype(GP::kWide)>> {
 // Orders the group's LDS accesses (one wave per workgroup: no barrier wait).
 __device__ inline void group_sync() { __syncthreads(); }
 
-// Hides a value from the optimizer at this point, so the LDS addresses formed
-// from a lane's constant tables are recomputed in each evaluation instead of
-// being hoisted out of the integration loop into ~100 extra live registers.
-__device__ inline void opaque(uint32_t& v) { asm volatile("" : "+v"(v)); }
-// The same for a double: the value is formed here, not later.
+// Hides a value from the optimizer at this point: it is formed here, not later.
 __device__ inline void opaque_f64(double& v) { asm volatile("" : "+v"(v)); }
 
 // The workgroup's exponential tables, after its groups' areas.
@@ -357,8 +353,28 @@ __device__ inline void load_row(const uint32_t* table, int row, uint32_t (&w)[Wo
   }
 }
 
+// The k-th of a row's packed byte offsets in the workgroup's areas (two to a
+// word), and the double there.
+template <int Words>
+__device__ inline uint32_t packed_at(const uint32_t (&w)[Words], int k) {
+  return k % 2 ? w[k / 2] >> 16 : w[k / 2] & 0xffffu;
+}
+template <class GP, int Words>
+__device__ inline double lds_packed(const Grp<GP>& x, const uint32_t (&w)[Words], int k) {
+  return *lds_at(x.areas + packed_at(w, k));
+}
+
 // Mass action: concentrations, [M] and rates of progress exchanged through
 // the group's LDS area (the scheme in the header comment).
+//
+// Bound: instruction issue, VALU (65 % of the cycles in RKCK at 53 species) and
+// LDS (73 %) alike.  An LDS address costs one instruction: half of a table word
+// that holds the lane's place in the wave's areas, against three for an index to
+// extract, scale and add to the group's area.  Reactions lie where reads meet
+// few bank conflicts (the generator's search).  A slot's operands and a batch
+// of eight terms are read ahead; with 168 registers RKCK runs three waves per
+// SIMD.  65536 systems, ms: 53 species RKCK 875 -> 646, RKC 669 -> 547; 32
+// species RKCK 768 -> 602, RKC 470 -> 349.
 template <class GP>
 __device__ void group_rhs_mass_action(const typename GP::Lane& L, const Grp<GP>& x,
                                       const double (&y)[GP::S], double (&f)[GP::S]) {
@@ -368,15 +384,15 @@ __device__ void group_rhs_mass_action(const typename GP::Lane& L, const Grp<GP>&
                     GP::kOffRed + GP::N <= GP::kOffQ + GP::kNegOff &&
                     GP::kOffQ + GP::kNegOff + GP::R * GP::kL <= GP::kLdsPerSystem,
                 "C, +q, the zero, the scratch and -q are disjoint");
-  constexpr int N = GP::N, LL = GP::kL;
+  constexpr int N = GP::N, kR = GP::R;
   double* const C = x.lds + GP::kOffC;
-  double* const Q = x.lds + GP::kOffQ;
-  // the operand and term tables are read from constant memory at each
-  // evaluation (vector loads, cached, issued here so that the exchanges below
-  // cover their latency), not held in registers across the integration
-  const int row = opaque_zero() + x.r;
-  uint32_t rxw[GP::kRxWords];
-  load_row<GP::kRxWords>(GP::kRx, row, rxw);
+  double* const Q = x.lds + GP::kOffQ + x.r;
+  // the addresses are read from constant memory at each evaluation (vector
+  // loads, cached, issued here so that the exchanges below cover their
+  // latency), not held in registers across the integration
+  const int row = opaque_zero() + (int)threadIdx.x;
+  uint32_t op[GP::kOpWords], tm[GP::kTmWords];
+  load_row<GP::kOpWords>(GP::kOp, row, op);
 #pragma unroll
   for (int m = 0; m < GP::S; ++m)
     if (owns<GP>(x, m)) C[x.sp[m]] = (L.rho * y[m]) * L.iW[m];
@@ -387,55 +403,64 @@ __device__ void group_rhs_mass_action(const typename GP::Lane& L, const Grp<GP>&
   ChainSum<GP, N> chain(x, C);
   constexpr int kChainSteps = ChainSum<GP, N>::kLanes;
   static_assert(kChainSteps <= GP::kMSlot || GP::kMSlot == GP::R, "[M] formed before its slots");
+  const uint32_t m_at = lds_address(C) + 8 * N - x.areas;
   double M = 0.0;
-  uint32_t tcw[GP::kTcWords];
+  double a[2][4];   // a slot's operands, read one slot ahead
 #pragma unroll
-  for (int m = 0; m < GP::R; ++m) {
+  for (int q = 0; q < 4; ++q) a[0][q] = lds_packed(x, op, q);
+#pragma unroll
+  for (int m = 0; m < kR; ++m) {
     if (m < kChainSteps) chain.step();
     if (m == kChainSteps - 1) {
       M = chain.result();
-      load_row<GP::kTcWords>(GP::kTc, row, tcw);
+      load_row<GP::kTmWords>(GP::kTm, row, tm);
     }
-    const int p = m * LL + x.r;
-    const uint32_t code = rxw[m];
-    const uint32_t ib = (code >> 8) & 0xffu, id = code >> 24;
-    const double ca = C[code & 0xffu], cc = C[(code >> 16) & 0xffu];
-    double cb = C[ib], cd = C[id];
+    double (&c)[4] = a[m % 2];
+    if (m + 1 < kR)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a[(m + 1) % 2][q] = lds_packed(x, op, 4 * m + 4 + q);
     if (m >= GP::kMSlot) {
       // a one-species side: its second factor is [M]
-      cb = ib == (uint32_t)N ? M : cb;
-      cd = id == (uint32_t)N ? M : cd;
+      c[1] = packed_at(op, 4 * m + 1) == m_at ? M : c[1];
+      c[3] = packed_at(op, 4 * m + 3) == m_at ? M : c[3];
     }
-    const double q = (L.kf[m] * ca) * cb - (L.kr[m] * cc) * cd;
-    Q[p] = q;
-    Q[GP::kNegOff + p] = -q;
-    // bound how far the scheduler moves loads ahead (register pressure)
-    if (m % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+    const double q = (L.kf[m] * c[0]) * c[1] - (L.kr[m] * c[2]) * c[3];
+    Q[m * GP::kL] = q;
+    Q[m * GP::kL + GP::kNegOff] = -q;
+    __builtin_amdgcn_sched_barrier(0);
   }
   group_sync();
-  // each lane's signed rates: its slot-0 species' terms (padded to whole
-  // chunks with the zero), then from chunk L.bnd on its slot-1 species'; the
-  // accumulator moves to slot 0 at the end of chunk L.bnd - 1
-  double acc = 0.0, om0 = 0.0;
+  // each lane's signed rates (om - q is formed as om + (-q)): its slot-0
+  // species' terms (padded to whole chunks with the zero), then from chunk
+  // L.bnd on its slot-1 species'; the accumulator moves to slot 0 at the end of
+  // chunk L.bnd - 1.  Read one batch ahead of the additions.
+  constexpr int kB = 8, kT = GP::kTermLen, kBatches = (kT + kB - 1) / kB;
+  double acc = 0.0, om0 = 0.0, next[kB];
 #pragma unroll
-  for (int t = 0; t < GP::kTermLen; ++t) {
-    // term t: kTermBits-bit position in the signed rates, packed
-    // kTermsPerWord to a register; om - q is formed as om + (-q)
-    const uint32_t word = tcw[t / GP::kTermsPerWord];
-    const uint32_t code = (word >> ((t % GP::kTermsPerWord) * GP::kTermBits)) &
-                          ((1u << GP::kTermBits) - 1u);
-    acc = acc + Q[code];
-    if (t % GP::kChunk == GP::kChunk - 1 && ((GP::kSwitchChunks >> (t / GP::kChunk)) & 1)) {
-      const bool sw = t / GP::kChunk + 1 == L.bnd;
-      om0 = sw ? acc : om0;
-      acc = sw ? 0.0 : acc;
+  for (int t = 0; t < kB; ++t)
+    if (t < kT) next[t] = lds_packed(x, tm, t);
+#pragma unroll
+  for (int b = 0; b < kBatches; ++b) {
+    double now[kB];
+#pragma unroll
+    for (int t = 0; t < kB; ++t) now[t] = next[t];
+#pragma unroll
+    for (int t = 0; t < kB; ++t)
+      if ((b + 1) * kB + t < kT) next[t] = lds_packed(x, tm, (b + 1) * kB + t);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < kB; ++u) {
+      const int t = b * kB + u;
+      if (t >= kT) continue;
+      acc = acc + now[u];
+      if (t % GP::kChunk == GP::kChunk - 1 && ((GP::kSwitchChunks >> (t / GP::kChunk)) & 1)) {
+        const bool sw = t / GP::kChunk + 1 == L.bnd;
+        om0 = sw ? acc : om0;
+        acc = sw ? 0.0 : acc;
+      }
     }
-    if (t % 16 == 15) {
-      // keep the additions near their loads (else all loads are issued first
-      // and held in registers; sixteen in flight: 6 % over four)
-      opaque_f64(acc);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    opaque_f64(acc);
+    __builtin_amdgcn_sched_barrier(0);
   }
   f[0] = owns<GP>(x, 0) ? (L.W[0] * om0) * L.irho : 0.0;
   f[1] = owns<GP>(x, 1) ? (L.W[1] * acc) * L.irho : 0.0;
@@ -477,12 +502,11 @@ __device__ double wide_terms(const typename GP::Lane& L) {
 // variant's two species per lane, whose instructions also serve two systems.
 // So it runs the batches whose slowest systems decide (times in ms, group
 // variant -> wide; RKCK spreads its step counts over a factor of twenty):
-//   53 species RKCK  200 systems 117 -> 46, 2048 207 -> 92, 16411 362 -> 272,
-//                    32768 552 -> 521, 65536 855 -> 930
-//   53 species RKC   200 systems 49 -> 27, 1024 59 -> 34, 2048 59 -> 57,
-//                    4096 68 -> 95
-//   32 species RKCK  200 systems 290 -> 110, 16411 395 -> 241, 65536 768 -> 679
-//   32 species RKC   200 systems 65 -> 33, 4096 83 -> 47, 16411 144 -> 131
+//   53 species RKCK  8192 systems 217 -> 171, 16384 382 -> 318, 32768 409 -> 465
+//   53 species RKC   1024 systems 48 -> 33, 2048 47 -> 58
+//   32 species RKCK  16384 systems 310 -> 236, 49152 550 -> 542, 65536 602 -> 650
+//   32 species RKC   2048 systems 60 -> 40, 4096 62 -> 48, 8192 67 -> 74
+// Hence kMaxRkck and kMaxRkc.
 // RKC at 53 species is compiled for one wave per SIMD (at two it spills 133
 // registers: 27 -> 37 ms at 200 systems).
 template <class GP>
@@ -567,7 +591,10 @@ __device__ void group_rhs_thermal(const typename GP::Lane& L, const Grp<GP>& x,
   double* const C = x.lds + GP::kOffC;
   double* const Q = x.lds + GP::kOffQ;
   const int z0 = opaque_zero();
-  const uint32_t* const rxl = GP::kRx + (z0 + x.r) * GP::kRxWords;
+  const int row = z0 + (int)threadIdx.x;
+  const uint32_t m_at = lds_address(C) + 8 * NS - x.areas;
+  uint32_t op[GP::kOpWords], tm[GP::kTmWords];
+  load_row<GP::kOpWords>(GP::kOp, row, op);
 #pragma unroll
   for (int m = 0; m < GP::S; ++m) {
     const int u = x.sp[m];
@@ -579,8 +606,7 @@ __device__ void group_rhs_thermal(const typename GP::Lane& L, const Grp<GP>& x,
   const double lnT = crm::cr_log(T);
   const double invT = 1.0 / T;
   const double M = group_chain_sum<GP, NS>(x, C);
-  uint32_t tcw[GP::kTcWords];
-  load_row<GP::kTcWords>(GP::kTc, z0 + x.r, tcw);
+  load_row<GP::kTmWords>(GP::kTm, row, tm);
   constexpr int K = GP::kExps, kB = (GP::R + K - 1) / K;
   const double2* const pr =
       reinterpret_cast<const double2*>(L.prm + GP::kPrmOffset + z0) + 2 * x.r;
@@ -611,13 +637,11 @@ __device__ void group_rhs_thermal(const typename GP::Lane& L, const Grp<GP>& x,
       const int m = b * K + k, pos = m * LL + x.r;
       if (m >= GP::R) continue;
       const double kr = kf[k] * iK[k];
-      const uint32_t code = rxl[m];
-      const uint32_t ib = (code >> 8) & 0xffu, id = code >> 24;
-      const double ca = C[code & 0xffu], cc = C[(code >> 16) & 0xffu];
-      double cb = C[ib], cd = C[id];
+      const double ca = lds_packed(x, op, 4 * m), cc = lds_packed(x, op, 4 * m + 2);
+      double cb = lds_packed(x, op, 4 * m + 1), cd = lds_packed(x, op, 4 * m + 3);
       if (m >= GP::kMSlot) {
-        cb = ib == (uint32_t)NS ? M : cb;
-        cd = id == (uint32_t)NS ? M : cd;
+        cb = packed_at(op, 4 * m + 1) == m_at ? M : cb;
+        cd = packed_at(op, 4 * m + 3) == m_at ? M : cd;
       }
       const double q = (kf[k] * ca) * cb - (kr * cc) * cd;
       Q[pos] = q;
@@ -629,11 +653,7 @@ __device__ void group_rhs_thermal(const typename GP::Lane& L, const Grp<GP>& x,
   double acc = 0.0, om0 = 0.0;
 #pragma unroll
   for (int t = 0; t < GP::kTermLen; ++t) {
-    uint32_t word = tcw[t / GP::kTermsPerWord];
-    opaque(word);
-    const uint32_t code = (word >> ((t % GP::kTermsPerWord) * GP::kTermBits)) &
-                          ((1u << GP::kTermBits) - 1u);
-    acc = acc + Q[code];
+    acc = acc + lds_packed(x, tm, t);
     if (t % GP::kChunk == GP::kChunk - 1 && ((GP::kSwitchChunks >> (t / GP::kChunk)) & 1)) {
       const bool sw = t / GP::kChunk + 1 == L.bnd;
       om0 = sw ? acc : om0;
@@ -678,11 +698,11 @@ __device__ void group_rhs_thermal(const typename GP::Lane& L, const Grp<GP>& x,
 // For small batches, bound by one evaluation's latency: half the rates, terms
 // and unknowns per lane and a whole SIMD's registers.  One wave per SIMD and
 // one system per wave, it loses once the 32-lane kernels fill both their waves.
-// RKC over 1e-6 s, ms here / 32 lanes per system: 53 species 1024 systems 92 /
-// 162, 2000 128 / 145, 4096 224 / 164; 32 species 1024 63 / 103, 2000 105 /
-// 105, 4096 185 / 120.  RKCK, whose few longest systems end the batch: 53
-// species 4096 586 / 808, 16384 1634 / 1769, 24576 2038 / 1842; 32 species 4096
-// 490 / 971, 8192 790 / 900, 16384 1191 / 1040.  Hence kMaxRkc and kMaxRkck.
+// RKC over 1e-6 s, ms here / 32 lanes per system: 53 species 1024 systems 91 /
+// 144, 1536 110 / 131, 2048 139 / 127; 32 species 1024 63 / 99, 1536 93 / 96,
+// 2048 114 / 98.  RKCK, whose few longest systems end the batch: 53 species 8192
+// 858 / 924, 12288 1100 / 1205, 24576 2038 / 1842; 32 species 4096 490 / 971,
+// 8192 789 / 780.  Hence kMaxRkc and kMaxRkck.
 template <class GP>
 __device__ void group_rhs_thermal_wide(const typename GP::Lane& L, const Grp<GP>& x,
                                   const double (&y)[GP::S], double (&f)[GP::S]) {
@@ -924,14 +944,20 @@ struct GRkc {
 
   // The attempt from its start (after an accepted step, a rejection's power
   // method, or the first evaluation) up to its first evaluation.
-  __device__ bool next_attempt(const Grp<GP>& x, const Ctl& c) {
-    if (!(t < c.t1)) return false;
-    if (attempts >= c.max_steps) {
-      status = kSysMaxSteps;
+  // One branch for every way to end here: each further one would copy the
+  // state it may change.
+  __device__ bool next_attempt(const Grp<GP>& x, const Ctl& c, bool finite = true) {
+    const bool more = t < c.t1, left = attempts < c.max_steps;
+    if (!(finite && more && left)) {
+      if (!finite)
+        status = kSysNonFinite;
+      else if (more)
+        status = kSysMaxSteps;
       return false;
     }
     h_want = h;
-    if (1.1 * h >= fabs(c.t1 - t)) h = fabs(c.t1 - t);
+    const double rest = fabs(c.t1 - t);
+    h = 1.1 * h >= rest ? rest : h;
     if (sr_phase == 0) {
       power_start(x, false);
       return true;
@@ -1073,11 +1099,7 @@ struct GRkc {
     gcopy<GP>(Fn, f);
     h = h * fmax(kP1, fac);
     h = fmax(c.hmin_rkc, fmin(c.hmax, h));
-    if (!group_all_finite<GP>(x, yn)) {
-      status = kSysNonFinite;
-      return false;
-    }
-    return next_attempt(x, c);
+    return next_attempt(x, c, group_all_finite<GP>(x, yn));
   }
 
   // The next advance runs the error estimate and the controller.
@@ -1193,6 +1215,7 @@ __device__ Grp<GP> group_of(double* lds) {
   Grp<GP> x;
   x.r = lane % GP::kL;
   x.lds = lds + g * GP::kLdsPerSystem;
+  x.areas = lds_address(lds);
   x.mask = ones << (g * GP::kL);
 #pragma unroll
   for (int m = 0; m < GP::S; ++m) x.sp[m] = GP::kSp[m * GP::kL + x.r];

@@ -61,11 +61,11 @@ def rk():
 @pytest.mark.parametrize("n_sp,method,n,t1,rtol,opts", [
     (53, "rkc", 1, 3e-8, 1e-8, {}),
     (53, "rkck", 3, 3e-8, 1e-8, {}),
-    (53, "rkc", 2048, 2e-9, 1e-8, {}),
-    (53, "rkc", 2049, 2e-9, 1e-8, {}),
+    (53, "rkc", 1024, 2e-9, 1e-8, {}),
+    (53, "rkc", 1025, 2e-9, 1e-8, {}),
     (32, "rkc", 3, 3e-8, 1e-8, dict(schedule=3)),
     (32, "rkck", 1025, 5e-9, 1e-8, dict(cost_order=1)),
-    (32, "rkc", 16385, 1e-9, 1e-8, {}),
+    (32, "rkc", 6145, 1e-9, 1e-8, {}),
     (53, "rkc", 24, 1e-5, 1e-3, {}),
     (32, "rkc", 24, 1e-5, 1e-3, {})])
 def test_wide_equals_oracle(rk, orc, n_sp, method, n, t1, rtol, opts):
@@ -111,3 +111,29 @@ def test_wide_carry(rk, n_sp, method):
         got.append([a.cpu().numpy() for a in (y, st, stats, carry[rows])])
     for a, b in zip(*got):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("n_sp,thermal", [(32, False), (53, False), (32, True), (53, True)])
+def test_packed_group_addresses(n_sp, thermal):
+    """The group kernels' packed LDS offsets name, for every lane of the wave,
+    the operands and terms of its group's layout in its group's area."""
+    net = I.standard_network(n_sp)
+    G = cg._group_layout(net, 32 if thermal else cg.group_lanes(n_sp), thermal=thermal)
+    L, R, per = G["L"], G["R"], G["lds_per_system"]
+    op, op_words, tm, tm_words = cg._packed_addresses(G)
+    assert op_words % 4 == 0 and tm_words % 4 == 0
+    assert sorted(j for j in G["rx_of"] if j >= 0) == list(range(net.n_rx))
+
+    def entry(table, words, lane, k):
+        return table[lane * words + k // 2] >> (16 * (k % 2)) & 0xffff
+
+    for lane in range(64):
+        r, area = lane % L, lane // L * per
+        for m in range(R):
+            for q in range(4):
+                want = G["rx"][m * L + r] >> (8 * q) & 255
+                assert entry(op, op_words, lane, 4 * m + q) == 8 * (area + want)
+        for t in range(G["tot"]):
+            code = (G["tc"][t // G["per_word"] * L + r] >> (t % G["per_word"] * G["bits"])
+                    & ((1 << G["bits"]) - 1))
+            assert entry(tm, tm_words, lane, t) == 8 * (area + G["off_q"] + code)
