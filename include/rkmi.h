@@ -394,7 +394,7 @@ typedef struct {
   int32_t mode;          /* RK_BATCH_* */
   int32_t waves_per_cu;  /* persistent grid: workgroups per compute unit; 0 = occupancy limit */
   int32_t order[4];      /* persistent: problem indices in the order waves take them;
-                            order[0] < 0 = largest networks first */
+                            order[0] < 0 = smallest networks first */
   int32_t refill[4];     /* persistent: idle lanes that trigger a refill, per problem; 0 = 16 */
   int32_t use_graph;     /* nonzero: capture the substeps in one HIP graph */
   int32_t reserved[4];   /* must be zero */

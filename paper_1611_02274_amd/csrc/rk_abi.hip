@@ -785,7 +785,10 @@ int batch_args(rk_batch b, const int64_t* n_sys, double* const* y, const double*
       a.net[e].stats = stats ? stats[k] : nullptr;
     }
   }
-  // order: as given, else the largest networks first
+  // order: as given, else the smallest networks first: theirs are the fewest
+  // waves (a lane per system) and the longest chains, which then run beside the
+  // larger networks' work instead of after it (four networks, 50000 systems,
+  // two substeps: 269 ms, largest first 292; 12000 systems 100 and 118)
   bool given = sched && sched->order[0] >= 0;
   if (given) {
     bool seen[rkmi::kBatchMaxNets] = {};
@@ -800,7 +803,7 @@ int batch_args(rk_batch b, const int64_t* n_sys, double* const* y, const double*
     for (int k = 0; k < b->n; ++k) idx[k] = k;
     for (int i = 0; i < b->n; ++i)
       for (int j = i + 1; j < b->n; ++j)
-        if (b->probs[idx[j]]->n_eq > b->probs[idx[i]]->n_eq) std::swap(idx[i], idx[j]);
+        if (b->probs[idx[j]]->n_eq < b->probs[idx[i]]->n_eq) std::swap(idx[i], idx[j]);
     for (int r = 0; r < b->n; ++r) a.order[r] = b->user_to_entry[idx[r]];
   }
   a.map = map;
