@@ -66,16 +66,30 @@ struct PleiadesProblem {
 // 7, with the smaller body index first as the one-lane code forms them), and
 // stored for both orders; each body's lane then sums its terms in the one-lane
 // order, so results equal the one-lane kernels.
+//
+// Bound: VALU issue (a square root and a division per pair).  Nothing branches:
+// a body's own term is (x_i - x_i) times a zero kept on the diagonal, which adds
+// +-0 to a sum that is never -0, and lane 7 repeats pairs of lanes 0..2 without a
+// body to sum for.  Positions lie as (x, y) and the pair values of a body in
+// rows of ten doubles, so all reads are of 16 bytes and the rows of a group's
+// lanes meet in no bank.  With a branch around each body's own term and reads of
+// single doubles, RKCK over ten steps took 19.9 ms at 262144 systems and 1.35 ms
+// at 2001, where now 18.9 and 1.03; RKC at 2001 systems 103, now 92.
+constexpr int kPleiadesRow = 10;   // doubles of a body's row of pair values
+// Pair p of the bodies a < b (p = 21: pair 0 again, for lane 7): the places of
+// their positions and of the pair's value in a group's area.
 struct PleiadesPairs {
-  int i[21], j[21];
-  constexpr PleiadesPairs() : i(), j() {
+  int16_t a[22], b[22];
+  constexpr PleiadesPairs() : a(), b() {
     int p = 0;
-    for (int a = 0; a < 7; ++a)
-      for (int b = a + 1; b < 7; ++b) {
-        i[p] = a;
-        j[p] = b;
+    for (int i = 0; i < 7; ++i)
+      for (int j = i + 1; j < 7; ++j) {
+        a[p] = (int16_t)i;
+        b[p] = (int16_t)j;
         ++p;
       }
+    a[21] = a[0];
+    b[21] = b[0];
   }
 };
 inline constexpr PleiadesPairs kPleiadesPairs{};
@@ -88,57 +102,74 @@ struct PleiadesGroup {
   static constexpr bool kColumns = false;
   static constexpr int kLaneDoubles = 0;
   static constexpr int S = 4;
+  // RKCK fits three waves per SIMD (four spill: 20.1 ms at 262144 systems); RKC
+  // two with a few spills (9000 systems: 122 ms, one wave 166)
+  static constexpr int kWavesPerEuRkck = 3;
+  static constexpr int kWavesPerEuRkc = 2;
   static constexpr bool kOwnRhs = true;
-  static constexpr int kOffPos = 0;               // x_1..x_7, y_1..y_7
-  static constexpr int kOffPair = 14;             // 1 / r_ij at i * 7 + j
-  static constexpr int kOffRed = kOffPair + 50;   // norm scratch, N doubles (16-byte aligned)
+  static constexpr int kOffPos = 0;                            // (x_i, y_i), lane 7's place
+  static constexpr int kOffPair = 16;                          // 1 / r_ij at i kPleiadesRow + j
+  static constexpr int kOffRed = kOffPair + 8 * kPleiadesRow;  // norm scratch, N doubles
   static constexpr int kLdsPerSystem = kOffRed + N;
   static constexpr int kSp[S * kL] = {0,  1,  2,  3,  4,  5,  6,  -1,     // x_r
                                       7,  8,  9,  10, 11, 12, 13, -1,     // y_r
                                       14, 15, 16, 17, 18, 19, 20, -1,     // x_r'
                                       21, 22, 23, 24, 25, 26, 27, -1};    // y_r'
   using Params = const double*;
-  struct Lane {};
-  __device__ static void init(Lane&, const Params&, const double* __restrict__, int64_t, int64_t,
-                              const Grp<PleiadesGroup>&) {}
-  __device__ static void rhs(const Lane&, const Grp<PleiadesGroup>& x, const double (&y)[S],
+  struct Lane {
+    int pa[3], pb[3], va[3], vb[3];   // its pairs' positions and values
+  };
+  __device__ static void init(Lane& L, const Params&, const double* __restrict__, int64_t,
+                              int64_t, const Grp<PleiadesGroup>& x) {
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      const int a = kPleiadesPairs.a[x.r + 7 * t], b = kPleiadesPairs.b[x.r + 7 * t];
+      L.pa[t] = a;
+      L.pb[t] = b;
+      L.va[t] = kOffPair + a * kPleiadesRow + b;
+      L.vb[t] = kOffPair + b * kPleiadesRow + a;
+    }
+    x.lds[kOffPair + x.r * (kPleiadesRow + 1)] = 0.0;   // the diagonal
+  }
+  __device__ static void rhs(const Lane& L, const Grp<PleiadesGroup>& x, const double (&y)[S],
                              double (&f)[S]) {
-    double* const P = x.lds + kOffPos;
-    double* const R = x.lds + kOffPair;
-    const bool body = x.r < 7;
-    if (body) {
-      P[x.r] = y[0];
-      P[7 + x.r] = y[1];
-    }
+    double2* const P = reinterpret_cast<double2*>(x.lds + kOffPos);
+    P[x.r] = make_double2(y[0], y[1]);
     group_sync();
-    if (body) {
+    double rinv[3];
 #pragma unroll
-      for (int t = 0; t < 3; ++t) {
-        const int p = x.r + 7 * t;
-        const int a = kPleiadesPairs.i[p], b = kPleiadesPairs.j[p];
-        const double xa = P[a], xb = P[b], ya = P[7 + a], yb = P[7 + b];
-        const double d2 = (xa - xb) * (xa - xb) + (ya - yb) * (ya - yb);
-        const double rinv = 1.0 / (d2 * sqrt(d2));
-        R[a * 7 + b] = rinv;
-        R[b * 7 + a] = rinv;
-      }
+    for (int t = 0; t < 3; ++t) {
+      const double2 a = P[L.pa[t]], b = P[L.pb[t]];
+      const double d2 = (a.x - b.x) * (a.x - b.x) + (a.y - b.y) * (a.y - b.y);
+      rinv[t] = 1.0 / (d2 * sqrt(d2));
+    }
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      x.lds[L.va[t]] = rinv[t];
+      x.lds[L.vb[t]] = rinv[t];
     }
     group_sync();
+    const double2* const row =
+        reinterpret_cast<const double2*>(x.lds + kOffPair + x.r * kPleiadesRow);
     double ax = 0.0, ay = 0.0;
-    if (body) {
 #pragma unroll
-      for (int j = 0; j < 7; ++j) {
-        if (j == x.r) continue;
-        const double rinv = R[x.r * 7 + j];
-        const double mj = (double)(j + 1);
-        ax += (mj * (P[j] - y[0])) * rinv;
-        ay += (mj * (P[7 + j] - y[1])) * rinv;
+    for (int q = 0; q < 4; ++q) {
+      const double2 r2 = row[q];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int j = 2 * q + h;
+        if (j == 7) continue;
+        const double2 p = P[j];
+        const double mj = (double)(j + 1), rj = h ? r2.y : r2.x;
+        ax += (mj * (p.x - y[0])) * rj;
+        ay += (mj * (p.y - y[1])) * rj;
       }
     }
+    const bool body = x.r < 7;
     f[0] = body ? y[2] : 0.0;
     f[1] = body ? y[3] : 0.0;
-    f[2] = ax;
-    f[3] = ay;
+    f[2] = body ? ax : 0.0;
+    f[3] = body ? ay : 0.0;
     group_sync();
   }
 };
