@@ -158,8 +158,9 @@ int rk_problem_create_mass_action(const rk_mech_desc *desc, rk_problem *out);
  * (per unit mass; u0, cv0, cv1: host arrays of n_sp, copied).  Available for
  * the topologies the code generator was given with the energy equation
  * (RK_EUNSUPPORTED otherwise): up to 15 species on the one-lane kernels of
- * every schedule; above, the group kernels (32 lanes per system) run under
- * every schedule and need the queue workspace of rk_workspace_bytes.  No
+ * every schedule; above, the group kernels (32 lanes per system, small batches
+ * 64) run under every schedule and need the queue workspace of
+ * rk_workspace_bytes.  No
  * adjoint. */
 int rk_problem_create_mass_action_thermal(const rk_mech_desc *desc, const double *u0,
                                           const double *cv0, const double *cv1,
@@ -177,7 +178,7 @@ int rk_problem_dims(rk_problem p, int32_t *n_eq, int32_t *n_param, int32_t *n_th
  * paper's intDriver, Sec. 3).  Persistent: a machine-sized grid whose lanes take
  * the next system from a device-side queue as soon as theirs is finished.
  * Group: for networks of more than 16 species, 16 lanes (up to 32 species)
- * or 32 lanes (more species) of a wave share one
+ * or 32 lanes (more species) of a wave, twice as many in small batches, share one
  * system (its vectors and rate constants spread over their registers, its
  * concentrations and rates exchanged through LDS), groups taking systems
  * from the queue; other problems run their default.  Auto: group where

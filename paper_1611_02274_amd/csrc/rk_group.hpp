@@ -367,8 +367,8 @@ __device__ inline double lds_packed(const Grp<GP>& x, const uint32_t (&w)[Words]
 // Mass action: concentrations, [M] and rates of progress exchanged through
 // the group's LDS area (the scheme in the header comment).
 //
-// Bound: instruction issue, VALU (65 % of the cycles in RKCK at 53 species) and
-// LDS (73 %) alike.  An LDS address costs one instruction: half of a table word
+// Bound: instruction issue, VALU (74 % of the cycles in RKCK at 53 species) and
+// LDS (82 %) alike.  An LDS address costs one instruction: half of a table word
 // that holds the lane's place in the wave's areas, against three for an index to
 // extract, scale and add to the group's area.  Reactions lie where reads meet
 // few bank conflicts (the generator's search).  A slot's operands and a batch
