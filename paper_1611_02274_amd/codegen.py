@@ -683,9 +683,8 @@ def _group_positions(net, L, R):
     plain = [j for j in range(nr) if j not in set(third)]
     m_slots = -(-len(third) // L) if third else 0
     # the [M] slots also take the plain reactions that do not fit before them
+    # (R slots hold all reactions, so what is left of these fits there)
     m_first = R - m_slots
-    while m_first > 0 and len(plain) > m_first * L:
-        m_first -= 1
     front = plain[:m_first * L]
     back = plain[m_first * L:] + third
     assert len(back) <= (R - m_first) * L

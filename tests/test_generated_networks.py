@@ -1,0 +1,64 @@
+"""Networks other than the standard four through the code generator: the
+sources it writes for them compile for the device (the layouts' static
+assertions hold) and their tables name every reaction once."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_1611_02274_amd import build
+from paper_1611_02274_amd import codegen as cg
+from paper_1611_02274_amd import inputs as I
+
+
+def network(n_sp, n_rx, n_third, seed=1):
+    """A topology of n_rx reactions between two and two species, n_third of them
+    with a one-species side (times [M])."""
+    rng = np.random.default_rng(seed)
+    reac, prod = np.zeros((n_rx, 2), np.int32), np.zeros((n_rx, 2), np.int32)
+    for j in range(n_rx):
+        s = rng.choice(n_sp, 4, replace=False)
+        reac[j], prod[j] = s[:2], s[2:]
+    prod[rng.choice(n_rx, n_third, replace=False), 1] = -1
+    z = np.zeros(n_rx)
+    return I.Network(n_sp=n_sp, n_rx=n_rx, comp=np.ones((n_sp, 3), np.int64), W=np.ones(n_sp),
+                     reac=reac, prod=prod, lnA=z, beta=z, Ea=z, Keq=z + 1.0)
+
+
+def hipcc(folder, text, *args):
+    """Compiles a device source that includes the kernels' headers; its output file."""
+    src, out = folder / "net.hip", folder / "net.out"
+    src.write_text(text)
+    r = subprocess.run([build.HIPCC, *build.CXXFLAGS, "--cuda-device-only", *args,
+                        str(src), "-o", str(out)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return out
+
+
+@pytest.fixture
+def folder(tmp_path):
+    # the generated headers include the kernels' headers from the folder above
+    (tmp_path / "gen").mkdir()
+    for f in os.listdir(build.CSRC):
+        if f.endswith(".hpp"):
+            (tmp_path / f).symlink_to(os.path.join(build.CSRC, f))
+    return tmp_path / "gen"
+
+
+# [M] sides that leave no room for every other reaction in the slots before
+# theirs, in the wide layout (all) and in the group layout (the last)
+@pytest.mark.parametrize("n_sp,n_rx,n_third", [(17, 49, 16), (32, 96, 16), (53, 365, 92),
+                                               (17, 110, 13)])
+def test_third_body_slots(folder, n_sp, n_rx, n_third):
+    net = network(n_sp, n_rx, n_third)
+    for L, G in ((cg.group_lanes(n_sp), cg._group_layout(net, cg.group_lanes(n_sp))),
+                 (cg.wide_lanes(n_sp), cg._wide_layout(net, cg.wide_lanes(n_sp)))):
+        assert sorted(j for j in G["rx_of"] if j >= 0) == list(range(n_rx))
+        third = [p for p, j in enumerate(G["rx_of"])
+                 if j >= 0 and (net.reac[j][1] < 0 or net.prod[j][1] < 0)]
+        assert G["m_first"] == G["R"] - -(-n_third // L)
+        assert min(third) >= G["m_first"] * L
+    header, source = cg.rhs_source(net, "t")
+    (folder / "net_t.hpp").write_text(header)
+    hipcc(folder, source, "-fsyntax-only")
