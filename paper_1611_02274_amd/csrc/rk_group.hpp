@@ -403,6 +403,9 @@ __device__ void group_rhs_mass_action(const typename GP::Lane& L, const Grp<GP>&
   ChainSum<GP, N> chain(x, C);
   constexpr int kChainSteps = ChainSum<GP, N>::kLanes;
   static_assert(kChainSteps <= GP::kMSlot || GP::kMSlot == GP::R, "[M] formed before its slots");
+  // the terms' addresses are read in this slot (without [M] sides there may be
+  // fewer slots than steps of the chain, and [M] is not needed)
+  constexpr int kTermsSlot = (kChainSteps < kR ? kChainSteps : kR) - 1;
   const uint32_t m_at = lds_address(C) + 8 * N - x.areas;
   double M = 0.0;
   double a[2][4];   // a slot's operands, read one slot ahead
@@ -411,10 +414,8 @@ __device__ void group_rhs_mass_action(const typename GP::Lane& L, const Grp<GP>&
 #pragma unroll
   for (int m = 0; m < kR; ++m) {
     if (m < kChainSteps) chain.step();
-    if (m == kChainSteps - 1) {
-      M = chain.result();
-      load_row<GP::kTmWords>(GP::kTm, row, tm);
-    }
+    if (m == kChainSteps - 1) M = chain.result();
+    if (m == kTermsSlot) load_row<GP::kTmWords>(GP::kTm, row, tm);
     double (&c)[4] = a[m % 2];
     if (m + 1 < kR)
 #pragma unroll

@@ -62,3 +62,27 @@ def test_third_body_slots(folder, n_sp, n_rx, n_third):
     header, source = cg.rhs_source(net, "t")
     (folder / "net_t.hpp").write_text(header)
     hipcc(folder, source, "-fsyntax-only")
+
+
+# fewer reaction slots than lanes in [M]'s chain of sums: 53 species in 5 slots
+# (seven lanes), 17 in one (three), and one slot more than lanes
+@pytest.mark.parametrize("n_sp,n_rx", [(53, 150), (17, 16), (53, 250)])
+def test_term_addresses_are_read(folder, n_sp, n_rx):
+    """The right-hand side reads the table of its terms' LDS addresses however
+    few reaction slots it has (the object holds the table only if it does)."""
+    net = network(n_sp, n_rx, 0)
+    header, _ = cg.rhs_source(net, "t")
+    (folder / "net_t.hpp").write_text(header)
+    asm = hipcc(folder, '''#include "net_t.hpp"
+using GP = rkmi::gen_t::GNet;
+__global__ void rhs(GP::Lane L, double* y) {
+  __shared__ __attribute__((aligned(16))) double lds[rkmi::group_lds_doubles<GP>()];
+  const rkmi::Grp<GP> x = rkmi::group_of<GP>(lds);
+  double a[GP::S], f[GP::S];
+  for (int m = 0; m < GP::S; ++m) a[m] = y[m * 64 + threadIdx.x];
+  rkmi::group_rhs_mass_action<GP>(L, x, a, f);
+  for (int m = 0; m < GP::S; ++m) y[m * 64 + threadIdx.x] = f[m];
+}
+''', "-S")
+    text = asm.read_text()
+    assert "kOp" in text and "kTm" in text
