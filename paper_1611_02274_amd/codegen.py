@@ -125,10 +125,12 @@ def rhs_source(net, tag: str) -> tuple[str, str]:
                 lines.append(f"    om[{int(k)}] += q;")
     body = "\n".join(lines)
     vjp = "" if columns else _vjp_source(net) + _gershgorin_source(net)
-    wide = "" if columns else _wide_source(net, body)
+    runs = 0 if columns else sparse_runs(net)
+    wide = _sparse_source(net, body, runs) if runs else ""
     group = group_source(net, tag) + wide_source(net, tag) if columns else ""
     fast = (f"template <>\nstruct {'FastVariant' if columns else 'SparseVariant'}<gen_{tag}::Net> "
-            f"{{\n  using type = gen_{tag}::{'GNet' if columns else 'NetR'};\n}};\n\n")
+            f"{{\n  using type = gen_{tag}::{'GNet' if columns else 'NetR'};\n}};\n\n"
+            if columns or runs else "")
     if columns:
         launch_call = (f"rkmi::launch_with_wide<rkmi::gen_{tag}::Net, rkmi::gen_{tag}::GNet, "
                        f"rkmi::gen_{tag}::WNet>(a, s)")
@@ -247,7 +249,26 @@ def _registers(body: str) -> str:
     return re.sub(r"kr = kf \* ld_uniform\(iK, (\d+)\);", r"kr = L.kr[\1];", body)
 
 
-def _wide_source(net, body: str) -> str:
+def sparse_runs(net) -> int:
+    """Which kernels of a one-lane network run its sparse variant (rk_device.hpp
+    SparseRuns): those whose values fit the 256 doubles of a lane's 512 registers
+    beside the rate constants.  Forward RKC: the recursion's vectors, the
+    concentrations and the sums, eight doubles per species.  RKCK holds its
+    stages at once, eleven per species, and needs room for a stage's products.
+    The reverse sweeps add a gradient per reaction.  Times without and with the
+    variant at 16000 systems, n species / reactions, ms:
+      RKC forward   16/50 23.3, 23.0; 16/60 175, 163; 16/70 97.6, 101
+      RKCK forward  12/30 2.61, 2.59; 13/27 1.19, 1.17; 12/40 1.75, 1.89 (8000
+                    systems); 16/30 2.53, 3.52; 16/50 1.93, 5.19
+      RKC reverse   13/27 20.6, 19.3; 16/30 45.3, 40.2; 15/36 87.8, 82.4; 14/44
+                    58.3, 68.3; 16/50 67, 106
+      RKCK reverse  9/19 9.74, 8.56; 13/27 (65536 systems) 15.3, 18.6"""
+    n, nr = net.n_sp, net.n_rx
+    return ((2 * nr + 11 * n <= 200) | (2 * nr + 8 * n <= 256) << 1 |
+            (3 * nr + 6 * n <= 128) << 2 | (3 * nr + 6 * n <= 200) << 3)
+
+
+def _sparse_source(net, body: str, runs: int) -> str:
     """The network with both rate constants of every reaction in registers,
     compiled for one wave per SIMD: batches that do not put a second wave on a
     SIMD (rk_device.hpp SparseVariant)."""
@@ -257,10 +278,8 @@ def _wide_source(net, body: str) -> str:
 // rate constants of every reaction stay in registers (no LDS read of k_f, no
 // scalar load of 1/K, no k_r product per evaluation).  9 species RKC, 300 systems
 // 21.5 -> 16.4 ms, RKCK 5001 13.4 -> 10.2 ms; 13 species RKC 65536 systems 13.8 ->
-// 12.1 ms, its reverse sweep 2^16 systems 23.3 -> 22.2 ms.  The RKCK reverse
-// sweep holds six stages' arguments and adjoints: 9 species gain (65536 forward
-// and back 91.9 -> 84.7 ms), at 13 the constants do not fit (216 registers
-// spilled, 15.3 -> 18.6 ms).
+// 12.1 ms, its reverse sweep 2^16 systems 23.3 -> 22.2 ms; 9 species RKCK forward
+// and back, 65536 systems, 91.9 -> 84.7 ms.
 struct NetR {{
   static constexpr int N = Net::N;
   static constexpr int NR = Net::NR;
@@ -268,7 +287,8 @@ struct NetR {{
   static constexpr int kGroupLanes = 1;
   static constexpr int kLaneDoubles = NR;   // set-up only
   static constexpr int kWavesPerEu = 1;
-  static constexpr bool kSweepRkck = {"true" if 3 * net.n_rx + 6 * net.n_sp <= 128 else "false"};
+  // kernels whose registers it fits (forward RKCK, RKC, then the reverse sweeps)
+  static constexpr int kRuns = {runs};
   using Params = Net::Params;
   struct Lane {{
     double kf[NR], kr[NR];

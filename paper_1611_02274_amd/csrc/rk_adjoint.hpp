@@ -471,16 +471,6 @@ __global__ void adjoint_keys_kernel(const int32_t* __restrict__ count, int64_t n
   keys[(int64_t)kStReject * n + i] = 0;
 }
 
-// Whether a sparse variant also runs the RKCK reverse sweep (kSweepRkck).
-template <class P, class = void>
-struct SparseSweepRkck {
-  static constexpr bool value = true;
-};
-template <class P>
-struct SparseSweepRkck<P, std::void_t<decltype(P::kSweepRkck)>> {
-  static constexpr bool value = P::kSweepRkck;
-};
-
 template <class Prob>
 int launch_taped(const LaunchArgs* a, const TapeArgs* t, void* stream) {
   static_assert(!Prob::kColumns, "the adjoint keeps the system's vectors in registers");
@@ -500,11 +490,12 @@ int launch_taped(const LaunchArgs* a, const TapeArgs* t, void* stream) {
     kernel<<<waves, dim3(kLdsStride), 0, s>>>(a->prm, a->n, a->y0, a->y1, a->g, a->ctl, a->status,
                                               a->stats, T, a->order, lanes);
   };
-  using Sparse = typename SparseVariant<Prob>::type;
   if (a->method == kMethodRkck)
-    sparse ? run(taped_kernel<Sparse, kMethodRkck>) : run(taped_kernel<Prob, kMethodRkck>);
+    run(sparse ? taped_kernel<Sparse<Prob, kMethodRkck>, kMethodRkck>
+               : taped_kernel<Prob, kMethodRkck>);
   else
-    sparse ? run(taped_kernel<Sparse, kMethodRkc>) : run(taped_kernel<Prob, kMethodRkc>);
+    run(sparse ? taped_kernel<Sparse<Prob, kMethodRkc>, kMethodRkc>
+               : taped_kernel<Prob, kMethodRkc>);
   return hipGetLastError() == hipSuccess ? kLaunchOk : kLaunchHip;
 }
 
@@ -550,14 +541,12 @@ int launch_adjoint(const AdjointArgs* a, void* stream) {
                                               a->dy0, a->dth, a->status,
                                               static_cast<double*>(a->ws), order, lanes);
   };
-  using Sparse = typename SparseVariant<Prob>::type;
-  // (a sparse variant that does not fit the RKCK sweep's registers leaves it to
-  // the network itself)
-  using SparseCk = typename std::conditional<SparseSweepRkck<Sparse>::value, Sparse, Prob>::type;
   if (ck)
-    sparse ? run(adjoint_kernel<SparseCk, kMethodRkck>) : run(adjoint_kernel<Prob, kMethodRkck>);
+    run(sparse ? adjoint_kernel<Sparse<Prob, kMethodRkck, true>, kMethodRkck>
+               : adjoint_kernel<Prob, kMethodRkck>);
   else
-    sparse ? run(adjoint_kernel<Sparse, kMethodRkc>) : run(adjoint_kernel<Prob, kMethodRkc>);
+    run(sparse ? adjoint_kernel<Sparse<Prob, kMethodRkc, true>, kMethodRkc>
+               : adjoint_kernel<Prob, kMethodRkc>);
   return hipGetLastError() == hipSuccess ? kLaunchOk : kLaunchHip;
 }
 

@@ -130,6 +130,23 @@ struct SparseVariant {
   using type = P;
 };
 
+// Whether a sparse variant runs the forward kernels (its kRuns, bit Method) or the
+// reverse sweep (bit Method + 2) of a method; all of them without such a mask.
+template <class S, int Method, bool kReverse, class = void>
+struct SparseRuns {
+  static constexpr bool value = true;
+};
+template <class S, int Method, bool kReverse>
+struct SparseRuns<S, Method, kReverse, std::void_t<decltype(S::kRuns)>> {
+  static constexpr bool value = (S::kRuns >> (Method + (kReverse ? 2 : 0))) & 1;
+};
+
+// The problem type whose kernel runs such a batch.
+template <class P, int Method, bool kReverse = false>
+using Sparse =
+    typename std::conditional<SparseRuns<typename SparseVariant<P>::type, Method, kReverse>::value,
+                              typename SparseVariant<P>::type, P>::type;
+
 // Controller state carried from one call to the next instead of the restart
 // (Sec. 3 mentions the alternative): rows of a [kCarryRows + N][n] array, the
 // RKC eigenvector estimate in the last N rows; RKCK uses kCarryValid and

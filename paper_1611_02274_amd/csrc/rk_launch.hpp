@@ -43,7 +43,7 @@ constexpr size_t block_col_bytes() {
 // 64 systems: 0.45 ms).  A second wave per SIMD costs more than it spreads
 // (2048 waves of two systems 0.49, 1024 of four 0.36 ms).  Systems in slot
 // columns keep 64 per wave (their workspace has a block per 64 systems).
-// *sparse: at most one wave per SIMD (the SparseVariant's case).
+// *sparse: at most one wave per SIMD (the sparse variant's case).
 template <class Prob>
 int spread_lanes(int64_t n, int* lanes, bool* sparse) {
   *lanes = kLdsStride;
@@ -117,7 +117,7 @@ int launch_method(const LaunchArgs* a, hipStream_t s) {
     if (spread_lanes<Prob>(a->n, &lanes, &sparse) != kLaunchOk) return kLaunchHip;
     const dim3 waves((unsigned)((a->n + lanes - 1) / lanes));
     if (sparse)
-      plain_kernel<typename SparseVariant<Prob>::type, Method, kPilot>
+      plain_kernel<Sparse<Prob, Method>, Method, kPilot>
           <<<waves, dim3(kLdsStride), 0, s>>>(prm, a->n, a->y0, a->y1, a->g, a->ctl, a->status,
                                               a->stats, cols, a->order, a->carry, lanes);
     else

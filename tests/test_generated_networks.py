@@ -86,3 +86,22 @@ __global__ void rhs(GP::Lane L, double* y) {
 ''', "-S")
     text = asm.read_text()
     assert "kOp" in text and "kTm" in text
+
+
+# forward RKCK, forward RKC, reverse RKCK, reverse RKC
+@pytest.mark.parametrize("n_sp,n_rx,want", [(9, 19, "1111"), (13, 27, "1101"), (12, 40, "0101"),
+                                            (16, 50, "0100"), (16, 70, "0000"),
+                                            (16, 100, "0000")])
+def test_sparse_variant_fits_registers(folder, n_sp, n_rx, want):
+    """Small batches take the variant with all rate constants in registers only
+    in the kernels that have room for them; the others run the network itself."""
+    header, _ = cg.rhs_source(network(n_sp, n_rx, 3), "t")
+    (folder / "net_t.hpp").write_text(header)
+    asserts = []
+    for k, bit in enumerate(want):
+        method, reverse = ("kMethodRkck", "kMethodRkc")[k % 2], ("false", "true")[k // 2]
+        net = "NetR" if bit == "1" else "Net"
+        asserts.append(f"static_assert(std::is_same<Sparse<gen_t::Net, {method}, {reverse}>, "
+                       f"gen_t::{net}>::value);")
+    hipcc(folder, '#include "net_t.hpp"\nnamespace rkmi {\n' + "\n".join(asserts) + "\n}\n",
+          "-fsyntax-only")
