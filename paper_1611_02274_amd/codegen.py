@@ -889,9 +889,10 @@ def _group_tables(G) -> str:
     op, op_words, tm, tm_words = _packed_addresses(G)
     return f"""{_table("kSp", "int", G["sp"])}
 {_table("kRxOf", "int16_t", G["rx_of"])}
-  // each lane's LDS byte offsets in the wave's areas, two to a word, contiguous
-  // and 16-byte aligned (read as whole vectors at every evaluation): the rates'
-  // operands, the terms
+  // each lane's LDS offsets (in units of 2^kAddrShift bytes) in the wave's areas,
+  // two to a word, contiguous and 16-byte aligned (read as whole vectors at every
+  // evaluation): the rates' operands, the terms
+  static constexpr int kAddrShift = {_address_shift(G)};
   static constexpr int kOpWords = {op_words};
   static constexpr int kTmWords = {tm_words};
 {_table("kOp", "uint32_t", op, align=16)}
@@ -901,17 +902,25 @@ def _group_tables(G) -> str:
   static constexpr uint64_t kSwitchChunks = {G["switch"]}ull;"""
 
 
+def _address_shift(G) -> int:
+    """Unit of the packed LDS offsets: bytes, or doubles for areas beyond 64 KiB
+    (networks of about a thousand reactions), whose reads then cost a shift."""
+    return 0 if 8 * (64 // G["L"]) * G["lds_per_system"] <= 1 << 16 else 3
+
+
 def _packed_addresses(G):
-    """Byte offsets in a wave's LDS areas, two to a word, each lane's words
-    contiguous and padded to whole 16-byte vectors: its rate operands (four per
-    slot) and the terms of its species' sums, from the layout's codes.  Returns
-    (operand words, words per lane, term words, words per lane)."""
+    """Offsets in a wave's LDS areas (_address_shift), two to a word, each lane's
+    words contiguous and padded to whole 16-byte vectors: its rate operands (four
+    per slot) and the terms of its species' sums, from the layout's codes.
+    Returns (operand words, words per lane, term words, words per lane)."""
     L, R, bits, per_word = G["L"], G["R"], G["bits"], G["per_word"]
+    unit = 8 >> _address_shift(G)
 
     def packed(entry, count):
         out = []
         for lane in range(64):
-            v = [8 * (entry(k, lane % L) + lane // L * G["lds_per_system"]) for k in range(count)]
+            v = [unit * (entry(k, lane % L) + lane // L * G["lds_per_system"])
+                 for k in range(count)]
             assert max(v) < 1 << 16
             v += [0] * (-count % 8)
             out += [a | b << 16 for a, b in zip(v[::2], v[1::2])]

@@ -1006,9 +1006,10 @@ struct GNet {
       75, -1, 67, 51, 80, 23, 121, 38, 45, 19, 95, 102, 46, 98, 41, 0,
       117, 2, 93, 123, 32, 101, 78, 71, 65, 3, 64, 73, 21, 1, 50, 74,
       88, 114, 116, 58, 25, -1, 79, 17, -1, 77, 113, 86, 90, 18, 66, -1};
-  // each lane's LDS byte offsets in the wave's areas, two to a word, contiguous
-  // and 16-byte aligned (read as whole vectors at every evaluation): the rates'
-  // operands, the terms
+  // each lane's LDS offsets (in units of 2^kAddrShift bytes) in the wave's areas,
+  // two to a word, contiguous and 16-byte aligned (read as whole vectors at every
+  // evaluation): the rates' operands, the terms
+  static constexpr int kAddrShift = 0;
   static constexpr int kOpWords = 20;
   static constexpr int kTmWords = 20;
   alignas(16) static constexpr uint32_t kOp[1280] = {

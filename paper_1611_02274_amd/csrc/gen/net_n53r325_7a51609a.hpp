@@ -2361,9 +2361,10 @@ struct GNet {
       310, 152, 211, 143, 176, 11, 273, 186, 60, 289, 182, 316, 145, 294, 236, 300,
       8, 25, -1, -1, 80, -1, 162, -1, -1, -1, 104, 322, -1, 215, -1, 231,
       -1, -1, -1, -1, -1, 122, 235, 245, -1, -1, 142, 276, 288, 295, 92, 123};
-  // each lane's LDS byte offsets in the wave's areas, two to a word, contiguous
-  // and 16-byte aligned (read as whole vectors at every evaluation): the rates'
-  // operands, the terms
+  // each lane's LDS offsets (in units of 2^kAddrShift bytes) in the wave's areas,
+  // two to a word, contiguous and 16-byte aligned (read as whole vectors at every
+  // evaluation): the rates' operands, the terms
+  static constexpr int kAddrShift = 0;
   static constexpr int kOpWords = 24;
   static constexpr int kTmWords = 24;
   alignas(16) static constexpr uint32_t kOp[1536] = {

@@ -23,12 +23,12 @@
 // [M]), the LDS layout (kOffC, kOffQ, kSentinel, kNegOff, kOffRed,
 // kLdsPerSystem: +q at kOffQ + p, the zero at kOffQ + kSentinel, -q at
 // kOffQ + kNegOff + p), the tables kSp (species of slot m of lane r at
-// m L + r, -1 for none), kOp and kTm (for each lane of the wave the LDS byte
-// offsets of its rates' operands, C_N standing for [M], and of its terms, two
-// to a word: its slot-0 species' list padded with the zero to whole chunks of
-// kChunk terms, then its slot-1 species' list, kTermLen in all), kBnd (the chunks
-// of the slot-0 list) and kSwitchChunks (the chunks at whose end some lane
-// switches), Params, Lane, init(Lane&, prm, g, i, n, x).
+// m L + r, -1 for none), kOp and kTm (for each lane of the wave the LDS offsets,
+// in units of 2^kAddrShift bytes, of its rates' operands, C_N standing for [M],
+// and of its terms, two to a word: its slot-0 species' list padded with the zero
+// to whole chunks of kChunk terms, then its slot-1 species' list, kTermLen in
+// all), kBnd (the chunks of the slot-0 list) and kSwitchChunks (the chunks at
+// whose end some lane switches), Params, Lane, init(Lane&, prm, g, i, n, x).
 #pragma once
 
 #include "rk_device.hpp"
@@ -353,15 +353,16 @@ __device__ inline void load_row(const uint32_t* table, int row, uint32_t (&w)[Wo
   }
 }
 
-// The k-th of a row's packed byte offsets in the workgroup's areas (two to a
-// word), and the double there.
+// The k-th of a row's packed offsets in the workgroup's areas (two to a word; in
+// bytes, or in doubles where the areas are larger than 64 KiB: kAddrShift), and
+// the double there.
 template <int Words>
 __device__ inline uint32_t packed_at(const uint32_t (&w)[Words], int k) {
   return k % 2 ? w[k / 2] >> 16 : w[k / 2] & 0xffffu;
 }
 template <class GP, int Words>
 __device__ inline double lds_packed(const Grp<GP>& x, const uint32_t (&w)[Words], int k) {
-  return *lds_at(x.areas + packed_at(w, k));
+  return *lds_at(x.areas + (packed_at(w, k) << GP::kAddrShift));
 }
 
 // Mass action: concentrations, [M] and rates of progress exchanged through
@@ -406,7 +407,7 @@ __device__ void group_rhs_mass_action(const typename GP::Lane& L, const Grp<GP>&
   // the terms' addresses are read in this slot (without [M] sides there may be
   // fewer slots than steps of the chain, and [M] is not needed)
   constexpr int kTermsSlot = (kChainSteps < kR ? kChainSteps : kR) - 1;
-  const uint32_t m_at = lds_address(C) + 8 * N - x.areas;
+  const uint32_t m_at = (lds_address(C) + 8 * N - x.areas) >> GP::kAddrShift;
   double M = 0.0;
   double a[2][4];   // a slot's operands, read one slot ahead
 #pragma unroll
@@ -593,7 +594,7 @@ __device__ void group_rhs_thermal(const typename GP::Lane& L, const Grp<GP>& x,
   double* const Q = x.lds + GP::kOffQ;
   const int z0 = opaque_zero();
   const int row = z0 + (int)threadIdx.x;
-  const uint32_t m_at = lds_address(C) + 8 * NS - x.areas;
+  const uint32_t m_at = (lds_address(C) + 8 * NS - x.areas) >> GP::kAddrShift;
   uint32_t op[GP::kOpWords], tm[GP::kTmWords];
   load_row<GP::kOpWords>(GP::kOp, row, op);
 #pragma unroll

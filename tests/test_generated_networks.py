@@ -105,3 +105,39 @@ def test_sparse_variant_fits_registers(folder, n_sp, n_rx, want):
                        f"gen_t::{net}>::value);")
     hipcc(folder, '#include "net_t.hpp"\nnamespace rkmi {\n' + "\n".join(asserts) + "\n}\n",
           "-fsyntax-only")
+
+
+@pytest.mark.parametrize("n_sp,n_rx,n_third,shift", [(24, 900, 500, 0), (32, 1000, 600, 3),
+                                                     (64, 2100, 1500, 3)])
+def test_packed_addresses_of_large_areas(folder, n_sp, n_rx, n_third, shift):
+    """Networks whose LDS areas exceed 64 KiB: the packed offsets count doubles,
+    and name every operand and term as for smaller ones."""
+    net = network(n_sp, n_rx, n_third)
+    L = cg.group_lanes(n_sp)
+    G = cg._group_layout(net, L)
+    assert cg._address_shift(G) == shift
+    op, op_words, tm, tm_words = cg._packed_addresses(G)
+
+    def at(table, words, lane, k):   # the double of the workgroup's areas
+        byte = (table[lane * words + k // 2] >> (16 * (k % 2)) & 0xffff) << shift
+        assert byte % 8 == 0
+        return byte // 8
+
+    seen = {j: p for p, j in enumerate(G["rx_of"]) if j >= 0}
+    assert len(seen) == n_rx
+    terms = cg._species_terms(net)
+    for lane in range(64):
+        r, area = lane % L, lane // L * G["lds_per_system"]
+        for m in range(G["R"]):
+            j = G["rx_of"][m * L + r]
+            want = [int(k) if k >= 0 else n_sp for k in (*net.reac[j], *net.prod[j])]
+            if j >= 0:
+                assert [at(op, op_words, lane, 4 * m + q) - area for q in range(4)] == want
+        got = [at(tm, tm_words, lane, t) - area - G["off_q"] for t in range(G["tot"])]
+        cut = G["bnd"][r] * G["chunk"]
+        for part, k in ((got[:cut], G["sp"][r]), (got[cut:], G["sp"][L + r])):
+            want = [seen[c >> 1] + G["neg"] * (c & 1) for c in (terms[k] if k >= 0 else [])]
+            assert part == want + [G["sentinel"]] * (len(part) - len(want))
+    header, source = cg.rhs_source(net, "t")
+    (folder / "net_t.hpp").write_text(header)
+    hipcc(folder, source, "-fsyntax-only")
