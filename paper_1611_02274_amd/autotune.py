@@ -4,8 +4,9 @@ Picks, by timing candidates on a seeded sample of the workload, the schedule
 of one network (plain / persistent / group, refill threshold, cost order,
 group alignment) or of a ragged
 batch (network order, per-network refill thresholds, workgroups per compute
-unit).  Results are cached per (network topologies, method, rtol, device) in a
-JSON file, so a workload is tuned once per machine.  Every candidate computes
+unit).  Results are cached per (network topologies, method, rtol, range of batch
+sizes that run the same kernels, device) in a JSON file, so a workload is tuned
+once per machine.  Every candidate computes
 the same bits (the schedules only change which lane runs which system when),
 so tuning never changes results.
 """
@@ -76,6 +77,47 @@ def sample_indices(n: int, fraction: float, minimum: int, seed: int) -> np.ndarr
     return np.sort(rng.choice(n, size=m, replace=False))
 
 
+def switch_line(problem, method: str, simds: int) -> int:
+    """Largest batch that may run other kernels than larger ones do: one-lane
+    problems are spread over the SIMDs and hand nothing out while all systems are
+    resident (64 to a wave, at most eight waves per SIMD); larger networks take
+    their wide variant; the others run one kernel at every size (0)."""
+    from . import codegen
+    if problem.n_eq <= codegen.REGISTER_SPECIES_LIMIT:
+        return 64 * 8 * simds
+    if problem.net is None:
+        return 0
+    return simds * codegen.wide_limit(problem.net.n_sp, problem.kind == "mass_action_thermal",
+                                      method)
+
+
+def network_sample(problem, method: str, n: int, simds: int, fraction: float, minimum: int,
+                   seed: int) -> np.ndarray:
+    """The systems to time for a batch of n: a sample that runs the kernels the
+    batch runs.  Above the switch line a sample stays above it; below, a one-lane
+    batch, whose systems per wave follow from its size, is taken whole."""
+    from . import codegen
+    line = switch_line(problem, method, simds)
+    if n > line:
+        minimum = max(minimum, line + 1)
+    elif problem.n_eq <= codegen.REGISTER_SPECIES_LIMIT:
+        minimum = n
+    return sample_indices(n, fraction, minimum, seed)
+
+
+def network_key(problem, method: str, n: int, simds: int, rtol: float) -> str:
+    """Cache key of a batch's best schedule, up to the device: above the switch
+    line one for all sizes, below it one per power of two."""
+    topo = problem.net.topology_key() if problem.net is not None else problem.kind
+    size = "large" if n > switch_line(problem, method, simds) else f"2^{(n - 1).bit_length()}"
+    return f"net/{topo}/{problem.n_eq}/{method}/{rtol:g}/{size}"
+
+
+def _simds() -> int:
+    import torch
+    return 4 * torch.cuda.get_device_properties(torch.cuda.current_device()).multi_processor_count
+
+
 NETWORK_CANDIDATES = (
     dict(schedule=1),                                   # plain, one lane per system
     dict(schedule=2, refill=8), dict(schedule=2, refill=16), dict(schedule=2, refill=32),
@@ -92,16 +134,17 @@ def tune_network(problem, method: str, y0, g, t0, t1, rtol, atol, fraction=0.05,
                  minimum=16384, seed=0, force=False) -> dict:
     """Best schedule for integrating this network: returns the keyword
     arguments for integrate_rkck / integrate_rkc (schedule, refill, cost order,
-    group alignment)."""
+    group alignment).  Times max(minimum, fraction * n) systems, or as many as it
+    takes for them to run the kernels that the whole batch runs."""
     import torch
 
     from . import integrate_rkc, integrate_rkck
-    topo = problem.net.topology_key() if problem.net is not None else problem.kind
-    key = f"net/{topo}/{method}/{rtol:g}/{_device_key()}"
+    simds = _simds()
+    key = f"{network_key(problem, method, y0.shape[1], simds, rtol)}/{_device_key()}"
     cached = _load().get(key)
     if cached and not force:
         return cached["best"]
-    idx = sample_indices(y0.shape[1], fraction, minimum, seed)
+    idx = network_sample(problem, method, y0.shape[1], simds, fraction, minimum, seed)
     ys = torch.from_numpy(np.ascontiguousarray(y0[:, idx])).cuda()
     gs = torch.from_numpy(np.ascontiguousarray(g[:, idx])).cuda()
     fn = integrate_rkck if method == "rkck" else integrate_rkc

@@ -565,8 +565,8 @@ struct WNet {{
   static constexpr bool kThermal = true;
   static constexpr bool kWide = true;
   // largest batches it runs, in systems per SIMD (rk_group.hpp group_rhs_thermal_wide)
-  static constexpr int kMaxRkck = {6 if n <= 32 else 12};
-  static constexpr int kMaxRkc = 1;
+  static constexpr int kMaxRkck = {wide_limit(n, True, 'rkck')};
+  static constexpr int kMaxRkc = {wide_limit(n, True, 'rkc')};
   static constexpr bool kExpTable = true;
   static constexpr int NS = {n};
   static constexpr int N = NS + 1;    // unknowns: T, then the species
@@ -1017,6 +1017,15 @@ struct GNet {{
 """
 
 
+def wide_limit(n_sp: int, thermal: bool, method: str) -> int:
+    """Systems per SIMD up to which a network's wide variant runs a batch
+    (measured on the 32- and 53-species networks, rk_group.hpp group_rhs_wide and
+    group_rhs_thermal_wide)."""
+    if thermal:
+        return 1 if method == "rkc" else 6 if n_sp <= 32 else 12
+    return (6 if n_sp <= 32 else 1) if method == "rkc" else 48 if n_sp <= 32 else 16
+
+
 def wide_lanes(n_sp: int) -> int:
     """Lanes per system of the wide variant: one species to a lane."""
     return 32 if n_sp <= 32 else 64
@@ -1074,8 +1083,8 @@ def wide_source(net, tag: str) -> str:
 struct WNet {{
   static constexpr bool kWide = true;
   // largest batches it runs, in systems per SIMD (rk_group.hpp group_rhs_wide)
-  static constexpr int kMaxRkck = {48 if n <= 32 else 16};
-  static constexpr int kMaxRkc = {6 if n <= 32 else 1};
+  static constexpr int kMaxRkck = {wide_limit(n, False, 'rkck')};
+  static constexpr int kMaxRkc = {wide_limit(n, False, 'rkc')};
   static constexpr int N = {n};
   static constexpr int NR = {G["nr"]};
   static constexpr int kL = {G["L"]};
