@@ -96,9 +96,19 @@ constexpr int64_t batch_col_block() {
   return m;
 }
 
+// The batch kernels give a lane its slot without the doubles a workgroup shares
+// in front of it (shared_area), and a group no table behind its areas.
+template <class Prob>
+constexpr bool batch_slots_suffice() {
+  static_assert(SharedDoubles<Prob>::value == 0,
+                "networks with the energy equation cannot enter a ragged batch");
+  return true;
+}
+
 template <class Prob>
 __device__ void batch_run_net(const BatchNet& d, Ctl c, int refill, unsigned long long* queue,
                               double* lds, double* colbase) {
+  static_assert(batch_slots_suffice<Prob>());
   c.refill = refill;
   if constexpr (Prob::kGroupLanes > 1) {
     group_persistent_loop<Prob, kMethodRkc>(d.prm, d.n, d.y, d.y, d.g, c, d.status, d.stats,
@@ -140,6 +150,7 @@ __global__ void batch_queue_reset(unsigned long long* queues, int n_net) {
 // of network slot_map[i] >> 28; each lane runs its own network's code.
 template <class Prob>
 __device__ void batch_plain_one(const BatchNet& d, const Ctl& c, int64_t local, double* slot) {
+  static_assert(batch_slots_suffice<Prob>());
   integrate_system<Prob, kMethodRkc>(d.prm, d.n, local, d.y, d.y, d.g, c, d.status, d.stats,
                                      slot, d.carry);
 }

@@ -141,3 +141,23 @@ def test_packed_addresses_of_large_areas(folder, n_sp, n_rx, n_third, shift):
     header, source = cg.rhs_source(net, "t")
     (folder / "net_t.hpp").write_text(header)
     hipcc(folder, source, "-fsyntax-only")
+
+
+@pytest.mark.parametrize("n_sp,kernel", [(13, "ragged_kernel"), (13, "interleaved_kernel"),
+                                         (53, "ragged_kernel")])
+def test_batches_refuse_the_energy_equation(folder, n_sp, kernel):
+    """The batch kernels form no exponentials' table: a batch of a network with
+    the energy equation does not compile, the isothermal one does."""
+    for thermal in (False, True):
+        net = I.thermal_network(n_sp)
+        header, _ = (cg.rhs_source(net, "t") if not thermal else cg.thermal_source(net, "t")
+                     if n_sp == 13 else cg.thermal_group_source(net, "t"))
+        (folder / "net_t.hpp").write_text(header)
+        name = "GNet" if thermal and n_sp == 53 else "Net"
+        text = (f'#include "net_t.hpp"\n#include "../rk_batch.hpp"\n'
+                f"void* f() {{ return (void*)rkmi::{kernel}<rkmi::gen_t::{name}>; }}\n")
+        if thermal:
+            with pytest.raises(AssertionError, match="cannot enter a ragged batch"):
+                hipcc(folder, text, "-fsyntax-only")
+        else:
+            hipcc(folder, text, "-fsyntax-only")
