@@ -1,0 +1,109 @@
+"""Batches on the large side of the sizes at which the launches change kernels:
+beyond one wave per SIMD, beyond what is resident (the queue), beyond the wide
+variants.  A few dozen to a few hundred systems, repeated to the batch's size (an
+odd number of them, so that a wave's lanes and groups hold every mixture), over
+short intervals; every copy equals the oracle bit for bit (the kernels do the
+oracle's operations in its order, with correctly rounded functions)."""
+import numpy as np
+import pytest
+
+from paper_1611_02274_amd import codegen as cg
+from paper_1611_02274_amd import inputs as I
+
+from .parity import say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rk():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1611_02274_amd as rk
+    return rk
+
+
+def simds():
+    import torch
+    return 4 * torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def problem(rk, orc, name, n, seed):
+    """(problem, oracle's problem, y0, g, atol) of n systems."""
+    if name == "vdp":
+        return rk.Problem.vdp(), orc.vdp(), *I.vdp_inputs(n, seed), 1e-10
+    n_sp = int(name[3:].split("_")[0])
+    if name.endswith("_thermal"):
+        net = I.thermal_network(n_sp)
+        return (rk.Problem.network_thermal(net), orc.network_thermal(net),
+                *I.thermal_inputs(net, n, seed), 1e-12)
+    net = I.standard_network(n_sp)
+    return rk.Problem.network(net), orc.network(net), *I.kinetics_inputs(net, n, seed), 1e-12
+
+
+def repeated(a, n):
+    """The systems of a, repeated to n, on the GPU."""
+    import torch
+    d = torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    return d.repeat(*([1] * (d.dim() - 1)), -(-n // d.shape[-1]))[..., :n].contiguous()
+
+
+def assert_copies(got, want, label):
+    """Every copy has the bits of want (NaN of any payload equal NaN)."""
+    import torch
+    want = repeated(want, got.shape[-1])
+    same = got == want
+    if got.dtype == torch.float64:
+        same = torch.where(torch.isnan(want), torch.isnan(got),
+                           got.view(torch.int64) == want.view(torch.int64))
+    assert bool(same.all()), (label, int((~same).sum()))
+
+
+def check(rk, orc, name, method, base, n, t1, rtol=1e-8, seed=51, carry=False, nan=False,
+          stages=0, **opts):
+    import torch
+    say(f"case large {name} {method} n={n} of {base} t1={t1} rtol={rtol} carry={carry} {opts}")
+    prob, pb, y0, g, atol = problem(rk, orc, name, base, seed)
+    if nan:
+        y0[3, 5] = np.nan
+    fg = rk.integrate_rkck if method == "rkck" else rk.integrate_rkc
+    y, gd = repeated(y0, n), repeated(g, n)
+    if carry:
+        cg_ = torch.zeros((rk.carry_rows(prob), n), dtype=torch.float64, device="cuda")
+        co = orc.carry_init(pb, base)
+        fo = orc.rkck_batch_carry if method == "rkck" else orc.rkc_batch_carry
+        for k in range(2):
+            y, st, stats = fg(prob, y, gd, k * t1, (k + 1) * t1, rtol, atol, carry=cg_, **opts)
+            y0, so, sto = fo(pb, y0, g, co, k * t1, (k + 1) * t1, rtol, atol)
+    else:
+        y, st, stats = fg(prob, y, gd, 0.0, t1, rtol, atol, out=y, **opts)   # in place
+        y0, so, sto = (orc.rkck_batch if method == "rkck" else orc.rkc_batch)(
+            pb, y0, g, 0.0, t1, rtol, atol)
+    torch.cuda.synchronize()
+    assert sto[5].max() > stages
+    assert_copies(st, so, "status")
+    assert_copies(stats, sto, "stats")
+    assert_copies(y, y0, "y")
+    if carry:
+        rows = slice(None) if method == "rkc" else slice(0, 2)
+        assert_copies(cg_[rows].contiguous(), np.ascontiguousarray(co[rows]), "carry")
+
+
+# more systems than eight waves of 64 on every SIMD: lanes take from the queue
+@pytest.mark.parametrize("name,method,t1,opts", [
+    ("vdp", "rkck", 0.5, dict(schedule=2)),
+    ("vdp", "rkck", 0.2, dict(schedule=0, carry=True)),
+    ("vdp", "rkc", 0.1, dict(schedule=2, refill=1, cost_order=1)),
+    ("net9", "rkc", 2e-8, dict(schedule=2, carry=True, cost_order=1)),
+    ("net13", "rkc", 2e-8, dict(schedule=2)),
+    ("net13", "rkc", 2e-8, dict(schedule=0, refill=64, carry=True)),
+    ("net13", "rkck", 5e-9, dict(schedule=2, cost_order=1)),
+    ("net9_thermal", "rkck", 2e-9, dict(schedule=2)),
+    ("net13_thermal", "rkc", 2e-9, dict(schedule=2, cost_order=1)),
+    ("net13_thermal", "rkc", 2e-9, dict(schedule=0, carry=True)),
+    # the plain kernels of more than one wave per SIMD
+    ("net9", "rkck", 5e-9, dict(schedule=1)),
+    ("net13_thermal", "rkck", 2e-9, dict(schedule=1, cost_order=1))])
+def test_queue(rk, orc, name, method, t1, opts):
+    check(rk, orc, name, method, 509, 8 * 64 * simds() + 65, t1, **opts)
