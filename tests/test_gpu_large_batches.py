@@ -107,3 +107,31 @@ def check(rk, orc, name, method, base, n, t1, rtol=1e-8, seed=51, carry=False, n
     ("net13_thermal", "rkck", 2e-9, dict(schedule=1, cost_order=1))])
 def test_queue(rk, orc, name, method, t1, opts):
     check(rk, orc, name, method, 509, 8 * 64 * simds() + 65, t1, **opts)
+
+
+# the kernels of more than one wave per SIMD; below, 48 systems per wave (columns
+# of a wave in two of the workspace's blocks), 16, and one partly filled wave
+@pytest.mark.parametrize("n_sp,method,per_simd", [
+    (9, "rkc", 64), (9, "rkck", 64), (13, "rkc", 64), (13, "rkck", 64),
+    (9, "rkc", 39), (9, "rkck", 39), (13, "rkc", 39), (13, "rkck", 39),
+    (9, "rkc", 1), (13, "rkck", 1), (9, "rkck", 0), (13, "rkc", 0)])
+def test_adjoint(rk, orc, n_sp, method, per_simd):
+    import torch
+    base, n = 131, per_simd * simds() + 67
+    say(f"case large adjoint {n_sp} {method} n={n}")
+    prob, pb, y0, g, atol = problem(rk, orc, f"net{n_sp}", base, 61)
+    w = I.adjoint_weights(n_sp, base, 61)
+    t1 = 2e-8
+    taped = rk.integrate_rkck_taped if method == "rkck" else rk.integrate_rkc_taped
+    gd = repeated(g, n)
+    y1, st, stats, tape = taped(prob, repeated(y0, n), gd, 0.0, t1, 1e-8, atol, max_accepted=4096,
+                                ckpt_every=8)
+    dy0, dth, ast = (rk.adjoint_rkck if method == "rkck" else rk.adjoint_rkc)(prob, gd, tape,
+                                                                            repeated(w, n))
+    torch.cuda.synchronize()
+    yo, d0, dt, so = (orc.rkck_adjoint_batch if method == "rkck" else orc.rkc_adjoint_batch)(
+        pb, y0, g, w, 0.0, t1, 1e-8, atol)
+    assert bool((ast == 0).all()) and torch.equal(tape.count, stats[0])
+    for got, want, label in ((st, so, "status"), (y1, yo, "y1"), (dy0, d0, "dy0"),
+                             (dth, dt, "dlnA")):
+        assert_copies(got, want, label)
