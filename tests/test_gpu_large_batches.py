@@ -135,3 +135,31 @@ def test_adjoint(rk, orc, n_sp, method, per_simd):
     for got, want, label in ((st, so, "status"), (y1, yo, "y1"), (dy0, d0, "dy0"),
                              (dth, dt, "dlnA")):
         assert_copies(got, want, label)
+
+
+# one system more than the wide variants run: the group kernels alone, with every
+# wait for the other groups of a wave, carried state, the cost order, steps of more
+# stages than the coefficient table holds and NaN input
+@pytest.mark.parametrize("name,method,base,t1,opts", [
+    ("net53", "rkc", 67, 3e-8, {}),
+    ("net53", "rkc", 67, 2e-8, dict(group_align=-1, schedule=3)),
+    ("net53", "rkc", 67, 2e-8, dict(group_align=8, refill=32, schedule=3)),
+    ("net53", "rkc", 67, 1e-8, dict(carry=True, cost_order=1)),
+    ("net53", "rkc", 24, 1e-5, dict(rtol=1e-3, nan=True, stages=32, seed=41)),
+    ("net53", "rkck", 67, 1e-9, {}),
+    ("net53", "rkck", 67, 5e-10, dict(carry=True, schedule=3)),
+    ("net53", "rkck", 67, 5e-10, dict(nan=True, cost_order=1)),
+    ("net32", "rkc", 67, 3e-8, dict(group_align=8)),
+    ("net32", "rkc", 67, 1e-8, dict(carry=True, group_align=-1)),
+    ("net32", "rkc", 24, 1e-5, dict(rtol=1e-3, nan=True, stages=32, seed=41)),
+    ("net32", "rkck", 67, 1e-9, {}),
+    ("net32", "rkck", 67, 1e-9, dict(schedule=3, refill=1, cost_order=1)),
+    ("net32", "rkck", 67, 5e-10, dict(carry=True, nan=True)),
+    ("net53_thermal", "rkc", 67, 1e-10, dict(cost_order=1)),
+    ("net53_thermal", "rkc", 67, 1e-10, dict(carry=True, group_align=8)),
+    ("net53_thermal", "rkck", 67, 2e-10, dict(nan=True)),
+    ("net32_thermal", "rkc", 67, 2e-10, dict(nan=True, group_align=-1)),
+    ("net32_thermal", "rkck", 67, 5e-10, dict(carry=True))])
+def test_group_kernels(rk, orc, name, method, base, t1, opts):
+    limit = cg.wide_limit(int(name[3:5]), name.endswith("_thermal"), method)
+    check(rk, orc, name, method, base, limit * simds() + 1, t1, **opts)
