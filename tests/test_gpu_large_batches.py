@@ -163,3 +163,24 @@ def test_adjoint(rk, orc, n_sp, method, per_simd):
 def test_group_kernels(rk, orc, name, method, base, t1, opts):
     limit = cg.wide_limit(int(name[3:5]), name.endswith("_thermal"), method)
     check(rk, orc, name, method, base, limit * simds() + 1, t1, **opts)
+
+
+@pytest.mark.parametrize("order", [[3, 2, 1, 0], [2, 0, 3, 1]])
+def test_batch_order(rk, order):
+    """A ragged batch's networks taken in other orders than the default."""
+    import torch
+    say(f"case batch order {order}")
+    _, per_net = I.ragged_inputs(2000, 9, (800.0, 3000.0))
+    batch = rk.Batch([rk.Problem.network(I.standard_network(k)) for k in (9, 13, 32, 53)])
+    got = []
+    for kw in ({}, dict(order=order)):
+        ys = [torch.from_numpy(y).cuda() for y, _ in per_net]
+        gs = [torch.from_numpy(g).cuda() for _, g in per_net]
+        st = [torch.empty(y.shape[1], dtype=torch.int32, device="cuda") for y in ys]
+        stats = [torch.empty((rk.RK_NSTATS, y.shape[1]), dtype=torch.int32, device="cuda")
+                 for y in ys]
+        batch.integrate_rkc(ys, gs, 0.0, 2e-7, 2, 1e-8, 1e-12, status=st, stats=stats, **kw)
+        torch.cuda.synchronize()
+        got.append([y.view(torch.int64) for y in ys] + st + stats)
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
