@@ -340,6 +340,8 @@ def thermal_source(net, tag: str) -> tuple[str, str]:
     # exponentials side by side: the divisor of the reactions, rounded up, in 3..5
     # that wastes least
     K = min((3, 4, 5), key=lambda k: (-nr % k, k))
+    # their tables in LDS beside the lanes' columns, unless these fill its 160 KiB
+    table = 64 * 8 * (nr + n + 1) + 8 * 128 <= 160 << 10
     lines = []
     for j in range(nr):
         r, p = net.reac[j], net.prod[j]
@@ -373,18 +375,18 @@ struct Net {{
   static constexpr int kGroupLanes = 1;
   static constexpr int kLaneDoubles = NR;
   static constexpr int kWavesPerEu = 2;
-  static constexpr bool kExpTable = true;
+  static constexpr bool kExpTable = {str(table).lower()};
   // uniform data: [lnA | beta | Ea | 1/K | W | 1/W | u0 | cv0 | cv1]
   using Params = const double*;
   struct Lane {{
     double* kf;
-    crm::ExpTable et;
+{"    crm::ExpTable et;" if table else "    crm::ExpConstants et;"}
     double rho, irho;
   }};
   RKMI_HD static void init(Lane& L, const Params&, const double* __restrict__ g, int64_t i,
                            int64_t, double* slot) {{
     L.kf = slot;
-    L.et.p = shared_area<Net>(slot);
+{"    L.et.p = shared_area<Net>(slot);" if table else ""}
     L.rho = g[i];
     L.irho = 1.0 / L.rho;
   }}

@@ -161,3 +161,19 @@ def test_batches_refuse_the_energy_equation(folder, n_sp, kernel):
                 hipcc(folder, text, "-fsyntax-only")
         else:
             hipcc(folder, text, "-fsyntax-only")
+
+
+@pytest.mark.parametrize("n_rx,table", [(302, "true"), (304, "false")])
+def test_energy_equation_fits_lds(folder, n_rx, table):
+    """One-lane networks with the energy equation whose columns leave no room in
+    LDS for the exponentials' table read the constants."""
+    header, _ = cg.thermal_source(network(15, n_rx, 3), "t")
+    (folder / "net_t.hpp").write_text(header)
+    hipcc(folder, '''#include "net_t.hpp"
+using namespace rkmi;
+using P = gen_t::Net;
+static_assert(P::kExpTable == %s);
+static_assert(8 * (kernel_lds_doubles<P, kMethodRkc>() * kLdsStride + SharedDoubles<P>::value) <=
+              160 << 10);
+void* f() { return (void*)plain_kernel<P, kMethodRkc>; }
+''' % table, "-fsyntax-only")
