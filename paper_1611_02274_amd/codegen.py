@@ -958,7 +958,8 @@ struct GNet {{
   static constexpr bool kColumns = false;
   static constexpr int kLaneDoubles = 0;
   // RKCK: three waves per SIMD, its loop fits 168 registers but for a few spills
-  // outside the evaluations (53 species, 65536 systems: 636 ms, two waves 698)
+  // outside the evaluations (53 species, 65536 systems, in one session: three waves
+  // 636 ms, two 698)
   static constexpr int kWavesPerEuRkc = 2;
   static constexpr int kWavesPerEuRkck = 3;
   static constexpr int S = {S};
@@ -1020,9 +1021,12 @@ struct GNet {{
 
 
 def wide_limit(n_sp: int, thermal: bool, method: str) -> int:
-    """Systems per SIMD up to which a network's wide variant runs a batch
-    (measured on the 32- and 53-species networks, rk_group.hpp group_rhs_wide and
-    group_rhs_thermal_wide)."""
+    """Systems per SIMD up to which a network's wide variant runs a batch: measured
+    on the 32- and 53-species networks (rk_group.hpp group_rhs_wide,
+    group_rhs_thermal_wide).  Seven networks of 17 to 60 species and 60 to 300
+    reactions, against the group kernels before the variant came: 1.04 to 2.8 times
+    faster up to these lines, but for 20 and 26 species RKCK at 48000 systems (0.94
+    and 0.97 times) and 60 species + T RKCK at 12000 (0.99)."""
     if thermal:
         return 1 if method == "rkc" else 6 if n_sp <= 32 else 12
     return (6 if n_sp <= 32 else 1) if method == "rkc" else 48 if n_sp <= 32 else 16

@@ -978,7 +978,8 @@ struct GNet {
   static constexpr bool kColumns = false;
   static constexpr int kLaneDoubles = 0;
   // RKCK: three waves per SIMD, its loop fits 168 registers but for a few spills
-  // outside the evaluations (53 species, 65536 systems: 636 ms, two waves 698)
+  // outside the evaluations (53 species, 65536 systems, in one session: three waves
+  // 636 ms, two 698)
   static constexpr int kWavesPerEuRkc = 2;
   static constexpr int kWavesPerEuRkck = 3;
   static constexpr int S = 2;

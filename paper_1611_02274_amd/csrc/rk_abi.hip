@@ -787,8 +787,10 @@ int batch_args(rk_batch b, const int64_t* n_sys, double* const* y, const double*
   }
   // order: as given, else the smallest networks first: theirs are the fewest
   // waves (a lane per system) and the longest chains, which then run beside the
-  // larger networks' work instead of after it (four networks, 50000 systems,
-  // two substeps: 269 ms, largest first 292; 12000 systems 100 and 118)
+  // larger networks' work instead of after it (four networks, 12000 systems, two
+  // substeps: 100 ms, largest first 118; 50000 systems 269 and 292; three substeps
+  // of 100000 systems 543 and 585, 300000 1511 and 1523; at 10^6 systems no order
+  // matters: 4822 and 4812)
   bool given = sched && sched->order[0] >= 0;
   if (given) {
     bool seen[rkmi::kBatchMaxNets] = {};

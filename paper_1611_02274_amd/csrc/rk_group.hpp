@@ -374,8 +374,8 @@ __device__ inline double lds_packed(const Grp<GP>& x, const uint32_t (&w)[Words]
 // extract, scale and add to the group's area.  Reactions lie where reads meet
 // few bank conflicts (the generator's search).  A slot's operands and a batch
 // of eight terms are read ahead; with 168 registers RKCK runs three waves per
-// SIMD.  65536 systems, ms: 53 species RKCK 875 -> 646, RKC 669 -> 547; 32
-// species RKCK 768 -> 602, RKC 470 -> 349.
+// SIMD.  65536 systems, ms: 53 species RKCK 895 -> 658 (646 to 680 over four
+// sessions), RKC 673 -> 551; 32 species RKCK 768 -> 602, RKC 470 -> 351.
 template <class GP>
 __device__ void group_rhs_mass_action(const typename GP::Lane& L, const Grp<GP>& x,
                                       const double (&y)[GP::S], double (&f)[GP::S]) {
@@ -1443,14 +1443,12 @@ __device__ void group_attempt_loop(const typename GP::Params& prm, int64_t n, co
   }
 }
 
-// Default of Ctl::align (the RKC state machine; RKCK groups run whole
-// attempts and stay in step): on the 53-species network at 2^16 systems the
-// RKC kernel took 760 / 742 / 753 / 767 ms with no waiting / 1 / 2 / 5 (32
-// species, four groups per wave: 505 / 472 / 525 / 590 ms with none / 1 / 3 /
-// 8).  With
-// the energy equation the evaluation (an exponential per reaction) outweighs
-// the controller, and waiting costs more than it saves (53 species + T at
-// 2^18 systems: 8.54 s without, 8.71 s with 1).
+// Default of Ctl::align (the RKC state machine; RKCK groups run whole attempts
+// and stay in step): at 2^16 systems RKC took 582 / 550 / 559 / 566 / 573 ms with
+// no waiting / 1 / 2 / 3 / 5 at 53 species, 391 / 351 / 369 / 388 / 416 ms at 32
+// (four groups per wave).  With the energy equation the evaluation (an exponential
+// per reaction) outweighs the controller, and waiting gains nothing (32768
+// systems, none / 1: 53 species + T 796 / 805 ms, 32 species + T 629 / 624).
 template <class GP, int Method>
 constexpr int group_align_default() {
   return GroupThermal<GP>::value ? 0 : 1;

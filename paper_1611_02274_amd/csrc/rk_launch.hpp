@@ -34,16 +34,19 @@ constexpr size_t block_col_bytes() {
 }
 
 // Systems per wave of a one-lane kernel over n systems: as few as still fit one
-// wave on every SIMD (64 from 256 systems per SIMD-wide row on).  A wave lasts
-// as long as its slowest system and runs every branch that one of its systems
-// takes, so a small batch is spread over the chip.  The other lanes repeat the
-// wave's systems (spread_position): with the mask left partly empty instead,
-// the same waves took 1.2x longer alone and 2.2x with one on every SIMD (van
-// der Pol, four systems a wave, 1024 waves: 0.91 against 0.36 ms; 64 waves of
-// 64 systems: 0.45 ms).  A second wave per SIMD costs more than it spreads
-// (2048 waves of two systems 0.49, 1024 of four 0.36 ms).  Systems in slot
-// columns keep 64 per wave (their workspace has a block per 64 systems).
-// *sparse: at most one wave per SIMD (the sparse variant's case).
+// wave on every SIMD (64 beyond 63 systems per SIMD).  A wave lasts as long as
+// its slowest system and runs every branch that one of its systems takes, so a
+// small batch is spread over the chip.  The other lanes repeat the wave's systems
+// (spread_position): with the mask left partly empty instead, the same waves took
+// 1.2x longer alone and 2.2x with one on every SIMD (van der Pol, four systems a
+// wave, 1024 waves: 0.91 against 0.36 ms; 64 waves of 64 systems: 0.45 ms).  A
+// second wave per SIMD costs more than it spreads (2048 waves of two systems 0.49,
+// 1024 of four 0.36 ms).  The choice is for a call that has the GPU: of several at
+// once on their own streams each fills the SIMDs (13 species RKC, 16384 systems
+// each, one / two / four streams: 10.6 / 19.3 / 35.1 ms, packed 64 to a wave 11.8 /
+// 16.7 / 17.2; 9 species, 300 systems: 17.3 / 18.6 / 28.2 and 28.9 / 29.8 / 31.5).
+// Systems in slot columns keep 64 per wave (their workspace has a block per 64
+// systems).  *sparse: at most one wave per SIMD (the sparse variant's case).
 template <class Prob>
 int spread_lanes(int64_t n, int* lanes, bool* sparse) {
   *lanes = kLdsStride;
