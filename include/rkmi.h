@@ -182,8 +182,8 @@ int rk_problem_dims(rk_problem p, int32_t *n_eq, int32_t *n_param, int32_t *n_th
  * Batches of up to 16 unknowns and at most 64 systems per SIMD are spread over
  * the whole GPU under either, a SIMD's share to a wave, whose other lanes repeat
  * it: the call alone is faster (1.1 to 1.7 times), but its waves fill the SIMDs,
- * so that more than two such calls at once on several streams take longer than
- * if each packed 64 systems to a wave.
+ * so that several such calls at once on their own streams may take longer (four:
+ * up to twice) than if each packed 64 systems to a wave.
  * Group: for networks of more than 16 species, 16 lanes (up to 32 species)
  * or 32 lanes (more species) of a wave, twice as many in small batches, share one
  * system (its vectors and rate constants spread over their registers, its
