@@ -179,11 +179,10 @@ int rk_problem_dims(rk_problem p, int32_t *n_eq, int32_t *n_param, int32_t *n_th
  * the next system from a device-side queue as soon as theirs is finished; a batch
  * of up to 16 unknowns that is resident as a whole leaves nothing to hand out and
  * runs the plain kernels (rk_options.refill has no effect then).
- * Batches of up to 16 unknowns and at most 64 systems per SIMD are spread over
- * the whole GPU under either, a SIMD's share to a wave, whose other lanes repeat
- * it: the call alone is faster (1.1 to 1.7 times), but its waves fill the SIMDs,
- * so that several such calls at once on their own streams may take longer (four:
- * up to twice) than if each packed 64 systems to a wave.
+ * Small batches of up to 16 unknowns are spread over the GPU under either, fewer
+ * than 64 systems to a wave, whose other lanes repeat them: van der Pol over all
+ * SIMDs, networks over at most half of them up to 64 systems per compute unit, so
+ * that calls on other streams run beside them.
  * Group: for networks of more than 16 species, 16 lanes (up to 32 species)
  * or 32 lanes (more species) of a wave, twice as many in small batches, share one
  * system (its vectors and rate constants spread over their registers, its

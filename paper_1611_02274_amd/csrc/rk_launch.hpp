@@ -33,20 +33,33 @@ constexpr size_t block_col_bytes() {
   return Prob::kColumns ? (size_t)slot_doubles<Prob, Method>() * kLdsStride * sizeof(double) : 0;
 }
 
-// Systems per wave of a one-lane kernel over n systems: as few as still fit one
-// wave on every SIMD (64 beyond 63 systems per SIMD).  A wave lasts as long as
+// Systems per wave of a one-lane kernel over n systems.  A wave lasts as long as
 // its slowest system and runs every branch that one of its systems takes, so a
 // small batch is spread over the chip.  The other lanes repeat the wave's systems
 // (spread_position): with the mask left partly empty instead, the same waves took
 // 1.2x longer alone and 2.2x with one on every SIMD (van der Pol, four systems a
-// wave, 1024 waves: 0.91 against 0.36 ms; 64 waves of 64 systems: 0.45 ms).  A
-// second wave per SIMD costs more than it spreads (2048 waves of two systems 0.49,
-// 1024 of four 0.36 ms).  The choice is for a call that has the GPU: of several at
-// once on their own streams each fills the SIMDs (13 species RKC, 16384 systems
-// each, one / two / four streams: 10.6 / 19.3 / 35.1 ms, packed 64 to a wave 11.8 /
-// 16.7 / 17.2; 9 species, 300 systems: 17.3 / 18.6 / 28.2 and 28.9 / 29.8 / 31.5).
-// Systems in slot columns keep 64 per wave (their workspace has a block per 64
-// systems).  *sparse: at most one wave per SIMD (the sparse variant's case).
+// wave, 1024 waves: 0.91 against 0.36 ms; 64 waves of 64 systems: 0.45 ms).
+// Cheap problems take as few systems as still fit one wave on every SIMD (64 beyond
+// 63 systems per SIMD; a second wave per SIMD costs more than it spreads: 2048 waves
+// of two systems 0.49, 1024 of four 0.36 ms).  Kernels that fill a SIMD's registers
+// (whole_simd) leave half of the SIMDs to batches on other streams, which find no
+// room beside them otherwise: one to two waves per compute unit, up to 64 systems
+// each.  On every SIMD instead, one call alone took 4-11 % less at 9 species RKC with
+// 1500 to 30000 systems and as long or up to 19 % longer elsewhere, but four calls at
+// once three times as long (ms, one / two / four streams, before any spreading, on
+// every SIMD, so): 13 species RKC 4096 systems 11.2 / 15.6 / 16.1, 9.5 / 17.8 / 33.2,
+// 9.7 / 10.0 / 10.5; 16384 systems RKCK 1.09 / 1.42 / 1.64, 1.17 / 1.71 / 2.76, 0.98 /
+// 1.21 / 1.36; 9 species RKC 4096 systems 30.7 / 40.4 / 42.0, 19.9 / 39.7 / 69.8, 22.2 /
+// 23.0 / 23.5; 13 species + T RKC 4096 systems 84 / 98 / 100, 42 / 79 / 148, 43 / 46 / 46.
+constexpr int systems_per_wave(int64_t n, int64_t cus, bool whole_simd) {
+  const int64_t l = whole_simd ? n / cus : (n + 4 * cus - 1) / (4 * cus);
+  return (int)(l < 1 ? 1 : l > kLdsStride ? kLdsStride : l);
+}
+
+// The same on the current device; a problem compiled for a stated number of waves
+// per SIMD is one whose registers leave no room beside them.  Systems in slot columns
+// keep 64 per wave (their workspace has a block per 64 systems).  *sparse: at most 64
+// systems per SIMD (the sparse variant's case).
 template <class Prob>
 int spread_lanes(int64_t n, int* lanes, bool* sparse) {
   *lanes = kLdsStride;
@@ -56,10 +69,8 @@ int spread_lanes(int64_t n, int* lanes, bool* sparse) {
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return kLaunchHip;
-  const int64_t simds = (int64_t)cus * 4;
-  const int64_t l = (n + simds - 1) / simds;
-  *lanes = (int)(l < 1 ? 1 : l > kLdsStride ? kLdsStride : l);
-  *sparse = l <= kLdsStride;
+  *lanes = systems_per_wave(n, cus, WavesPerEu<Prob>::value > 1);
+  *sparse = n <= (int64_t)kLdsStride * 4 * cus;
   return kLaunchOk;
 }
 

@@ -177,3 +177,27 @@ static_assert(8 * (kernel_lds_doubles<P, kMethodRkc>() * kLdsStride + SharedDoub
               160 << 10);
 void* f() { return (void*)plain_kernel<P, kMethodRkc>; }
 ''' % table, "-fsyntax-only")
+
+
+def test_small_batches_leave_room(folder):
+    """Up to 64 systems per compute unit, a batch of a one-lane network takes at
+    most half of the SIMDs (its kernels fill a SIMD's registers), so batches on
+    other streams run beside it; every batch is held in waves of 1 to 64 systems."""
+    header, source = cg.rhs_source(network(9, 19, 3), "t")
+    (folder / "net_t.hpp").write_text(header)
+    hipcc(folder, '''#include "net_t.hpp"
+#include "../rk_launch.hpp"
+using namespace rkmi;
+static_assert(WavesPerEu<gen_t::Net>::value > 1, "fills a SIMD");
+constexpr bool room(int64_t cus, bool whole_simd) {
+  for (int64_t n = 1; n <= 80 * 4 * cus; n += n < 70 * cus ? 1 : 97) {
+    const int64_t l = systems_per_wave(n, cus, whole_simd), waves = (n + l - 1) / l;
+    if (l < 1 || l > 64 || (waves > 4 * cus && l < 64)) return false;
+    if (whole_simd && n <= 64 * cus && waves > 2 * cus) return false;
+  }
+  return true;
+}
+static_assert(room(256, true) && room(256, false) && room(64, true));
+static_assert(systems_per_wave(4096, 256, false) == 4 && systems_per_wave(4096, 256, true) == 16);
+int f(const LaunchArgs* a, hipStream_t s) { return launch_method<gen_t::Net, kMethodRkc, false>(a, s); }
+''', "-fsyntax-only", "-fconstexpr-steps=20000000")

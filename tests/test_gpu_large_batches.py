@@ -109,11 +109,11 @@ def test_queue(rk, orc, name, method, t1, opts):
     check(rk, orc, name, method, 509, 8 * 64 * simds() + 65, t1, **opts)
 
 
-# the kernels of more than one wave per SIMD; below, 48 systems per wave (columns
-# of a wave in two of the workspace's blocks), 16, and one partly filled wave
+# the kernels of more than one wave per SIMD; below, reverse sweeps of 48 systems per
+# wave (columns of a wave in two of the workspace's blocks) and 16, few systems
 @pytest.mark.parametrize("n_sp,method,per_simd", [
     (9, "rkc", 64), (9, "rkck", 64), (13, "rkc", 64), (13, "rkck", 64),
-    (9, "rkc", 39), (9, "rkck", 39), (13, "rkc", 39), (13, "rkck", 39),
+    (9, "rkc", 10), (9, "rkck", 10), (13, "rkc", 10), (13, "rkck", 10),
     (9, "rkc", 1), (13, "rkck", 1), (9, "rkck", 0), (13, "rkc", 0)])
 def test_adjoint(rk, orc, n_sp, method, per_simd):
     import torch
