@@ -109,6 +109,15 @@ def test_queue(rk, orc, name, method, t1, opts):
     check(rk, orc, name, method, 509, 8 * 64 * simds() + 65, t1, **opts)
 
 
+# systems per wave of the networks' small batches, n / compute units: the first
+# wave of two, 63 with a last wave part full, 64, and one system in a last wave
+@pytest.mark.parametrize("name,method,t1", [("net9", "rkc", 2e-8), ("net13", "rkck", 5e-9),
+                                            ("net13_thermal", "rkc", 2e-9)])
+@pytest.mark.parametrize("per_cu,more", [(2, -1), (2, 0), (64, -1), (64, 1)])
+def test_spread_edges(rk, orc, name, method, t1, per_cu, more):
+    check(rk, orc, name, method, 67, per_cu * simds() // 4 + more, t1, schedule=1)
+
+
 # the kernels of more than one wave per SIMD; below, reverse sweeps of 48 systems per
 # wave (columns of a wave in two of the workspace's blocks) and 16, few systems
 @pytest.mark.parametrize("n_sp,method,per_simd", [
